@@ -459,6 +459,47 @@ static bool bonds_in_pass(const lb_ctx* c) {
   return c->gcap <= bx && c->ngroups <= slab;
 }
 
+// Cache policy of the pass, by the bytes of the two population buffers
+// against the 256 MB last-level cache.  Non-temporal stores bypass it, cached
+// ones stay; times are per pass without particles, non-temporal -> as chosen.
+//   32 to 290 MiB: the buffers (nearly) stay in the cache, so loads and stores
+//     are cached (FP32 96^3 27.2 -> 20.4 us, 117^3 45.9 -> 35.1; FP16 128^3
+//     36.1 -> 29.0; FP64 64^3 16.5 -> 13.1, 96 x 96 x 64 39.2 -> 24.1).  From 240 MiB
+//     the two buffers overflow it by a little and successive passes sweep in
+//     opposite directions, so that a pass starts on the rows written last
+//     (FP32 128 x 112 x 128 53.2 -> 47.1, FP64 96^3 52.6 -> 37.4; without the
+//     reversal 54.6 and 40.8).  Below 32 MiB the write-back of the cached
+//     lines at the end of the kernel costs more than it saves (FP32
+//     45 x 37 x 52: 6.0 against 6.6 us); at 304 MiB nothing is gained.
+//   500 to 1100 MiB, FP32 or FP64, rows of whole 128-byte lines: non-temporal
+//     loads, so that only what is written stays in the cache, and reversed
+//     sweeps that begin with it (FP32 192 x 160 x 160 136.6 -> 126.3, 160^3
+//     113 -> 104, 192^3 196 -> 191; FP64 128^3 136 -> 115).  Rows that share lines
+//     re-read them, which non-temporal loads make expensive (FP32 180^3 154
+//     against 161).  16-bit storage gains nothing.
+//     Nor does the binned immersed boundary, whose velocity and force fields
+//     take the cache between two passes (128 x 128 x 256 channel: no change).
+//   else non-temporal stores, and non-temporal loads for the FP32 row-mapped
+//     pass without noise (256^3: 441 -> 432 us; FP16 226 against 235, the
+//     linear-site pass 408 against 457).
+// Not for the comoving frame and the stress sweep, which stream.
+static void set_cache_policy(const lb_ctx* c, LatArgs& a) {
+  const int sb = storage_bytes(c->p.storage);
+  const double mib = 2.0 * Q * (double)c->geo.ps * sb / (1 << 20);
+  const bool lines = (long long)c->geo.nx * sb % 128 == 0;
+  a.cache = kStream;
+  a.reverse = 0;
+  if (c->p.comoving || c->sweep) return;
+  if (mib >= 32.0 && mib <= 290.0) {
+    a.cache = kResident;
+    a.reverse = mib > 240.0 ? (int)(c->steps & 1) : 0;
+  } else if (mib >= 500.0 && mib <= 1100.0 && lines && sb >= 4 && c->p.kT == 0.0 &&
+             !c->tiled) {
+    a.cache = kKeepWritten;
+    a.reverse = (int)(c->steps & 1);
+  }
+}
+
 // bond_nsub > 0: the launch also runs bond_nsub sub-steps of bond_dt of every
 // bond group (bonds_in_pass must hold).
 static lb_status lattice_pass(lb_ctx* c, int bond_nsub = 0, double bond_dt = 0.0) {
@@ -511,6 +552,7 @@ static lb_status lattice_pass(lb_ctx* c, int bond_nsub = 0, double bond_dt = 0.0
     const int groups = std::max(1, waves_cu / (bx / 64));
     a.occ_lds = (c->lds_cu / groups) & ~1023;
   }
+  set_cache_policy(c, a);
   a.mrt = c->p.collision == LB_MRT ? 1 : 0;
   {  // group rates: bulk, shear, vector, pseudo-vector, scalar and tensor ghosts
     const double* r = c->p.mrt_rates;

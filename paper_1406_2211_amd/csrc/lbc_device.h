@@ -119,8 +119,10 @@ struct Store<LB_F64> {
   // non-temporal load (the row-mapped pass reads each population once)
   static __device__ __forceinline__ R raw_nt(const T* p) { return __builtin_nontemporal_load(p); }
   // populations are written once per pass and not re-read by it: non-temporal
+  // (st_raw), unless the next pass finds them in the last-level cache (st_cached)
   static __device__ __forceinline__ void st(T* p, R v, R) { __builtin_nontemporal_store(v, p); }
   static __device__ __forceinline__ void st_raw(T* p, R v) { __builtin_nontemporal_store(v, p); }
+  static __device__ __forceinline__ void st_cached(T* p, R v) { *p = v; }
 };
 template <>
 struct Store<LB_F32> {
@@ -132,6 +134,7 @@ struct Store<LB_F32> {
   static __device__ __forceinline__ R raw_nt(const T* p) { return __builtin_nontemporal_load(p); }
   static __device__ __forceinline__ void st(T* p, R v, R) { __builtin_nontemporal_store(v, p); }
   static __device__ __forceinline__ void st_raw(T* p, R v) { __builtin_nontemporal_store(v, p); }
+  static __device__ __forceinline__ void st_cached(T* p, R v) { *p = v; }
 };
 template <>
 struct Store<LB_F16> {
@@ -148,6 +151,7 @@ struct Store<LB_F16> {
   static __device__ __forceinline__ void st_raw(T* p, R v) {
     __builtin_nontemporal_store(__half_as_ushort(__float2half_rn(v)), (unsigned short*)p);
   }
+  static __device__ __forceinline__ void st_cached(T* p, R v) { *p = __float2half_rn(v); }
 };
 template <>
 struct Store<LB_BF16> {
@@ -165,7 +169,17 @@ struct Store<LB_BF16> {
     const __hip_bfloat16 b = __float2bfloat16(v);
     __builtin_nontemporal_store(*(const unsigned short*)&b, (unsigned short*)p);
   }
+  static __device__ __forceinline__ void st_cached(T* p, R v) { *p = __float2bfloat16(v); }
 };
+
+// Store of one new population under a cache policy of the pass.
+template <int S, int CP>
+__device__ __forceinline__ void st_pop(typename Store<S>::T* p, typename Store<S>::R v) {
+  if constexpr (CP == kStream)
+    Store<S>::st_raw(p, v);
+  else
+    Store<S>::st_cached(p, v);
+}
 
 __device__ __forceinline__ long long site_index(const Geo& g, int x, int y, int z) {
   return ((long long)z * g.ny + y) * g.nx + x;
@@ -489,7 +503,7 @@ __host__ __device__ inline const float* pick_terms<float>(const double*, const f
 // so neither the loads nor the stores need the scale; the U terms are
 // per-pass constants (comoving_terms).
 // With NS the thermal noise of site_noise is added to every stored value.
-template <int S, bool CM, bool NS = false, bool SG = false>
+template <int S, bool CM, bool NS = false, bool SG = false, int CP = kStream>
 __device__ __forceinline__ void fused_site(const typename Store<S>::R f[Q], typename Store<S>::R Fx,
                                            typename Store<S>::R Fy, typename Store<S>::R Fz,
                                            const PassK<typename Store<S>::R>& k,
@@ -533,7 +547,7 @@ __device__ __forceinline__ void fused_site(const typename Store<S>::R f[Q], type
     }
     R v = eh + R(2) * k.hp * (f[0] - eb);
     if (NS) v += nz[0];
-    St::st_raw(fo + own, v);
+    st_pop<S, CP>(fo + own, v);
   }
 #pragma unroll
   for (int i = 1; i < Q; i += 2) {
@@ -566,8 +580,8 @@ __device__ __forceinline__ void fused_site(const typename Store<S>::R f[Q], type
       if (CX[i] && CZ[i]) pxz += R(CX[i] * CZ[i]) * s2;
       if (CY[i] && CZ[i]) pyz += R(CY[i] * CZ[i]) * s2;
     }
-    St::st_raw(fo + (size_t)i * P + own, vi);
-    St::st_raw(fo + (size_t)(i + 1) * P + own, vj);
+    st_pop<S, CP>(fo + (size_t)i * P + own, vi);
+    st_pop<S, CP>(fo + (size_t)(i + 1) * P + own, vj);
   }
   if (SG) {  // viscous stress of the state this pass started from (Eq. viscstress)
     const R pf = sp * k.inv;
@@ -631,7 +645,7 @@ constexpr double mrt_inv_b(int k) {
 // over the opposite pairs: even rows see n_i + n_j, odd rows n_i - n_j.  The
 // row coefficients are compile-time integers, so only their nonzero terms
 // are formed.
-template <int S, bool NS>
+template <int S, bool NS, int CP = kStream>
 __device__ __forceinline__ void fused_site_mrt(const typename Store<S>::R f[Q],
                                                typename Store<S>::R Fx, typename Store<S>::R Fy,
                                                typename Store<S>::R Fz,
@@ -723,7 +737,7 @@ __device__ __forceinline__ void fused_site_mrt(const typename Store<S>::R f[Q],
 #pragma unroll
     for (int q = 4; q < Q; ++q)
       if (!mrt_odd(q) && mrt_row(q, 0) != 0) c += R(mrt_row(q, 0)) * D[q];
-    St::st_raw(fo + own, eh0 + n0 - wgt<R>(0) * c);
+    st_pop<S, CP>(fo + own, eh0 + n0 - wgt<R>(0) * c);
   }
 #pragma unroll
   for (int p = 0; p < 9; ++p) {
@@ -739,8 +753,8 @@ __device__ __forceinline__ void fused_site_mrt(const typename Store<S>::R f[Q],
         ce += R(c) * D[q];
     }
     const R w = wgt<R>(i);
-    St::st_raw(fo + (size_t)i * P + own, Eh[p] + Oh[p] + nI[p] - w * (ce + co));
-    St::st_raw(fo + (size_t)(i + 1) * P + own, Eh[p] - Oh[p] + nJ[p] - w * (ce - co));
+    st_pop<S, CP>(fo + (size_t)i * P + own, Eh[p] + Oh[p] + nI[p] - w * (ce + co));
+    st_pop<S, CP>(fo + (size_t)(i + 1) * P + own, Eh[p] - Oh[p] + nJ[p] - w * (ce - co));
   }
 }
 

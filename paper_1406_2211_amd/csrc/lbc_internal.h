@@ -34,6 +34,11 @@ struct BondArgs {
   int type;
 };
 
+// Population loads and stores of the lattice pass: kStream non-temporal stores
+// (and loads, for the FP32 row-mapped pass without noise), kResident cached
+// loads and stores, kKeepWritten non-temporal loads and cached stores.
+enum CachePolicy { kStream = 0, kResident = 1, kKeepWritten = 2 };
+
 // Fused lattice pass (stream, both pending half forces, collide).
 struct LatArgs {
   Geo g;
@@ -63,6 +68,8 @@ struct LatArgs {
   // amplitude S sqrt(mu lambda (2 - lambda)) of each group
   int mrt;
   double lg[6], ag[6];
+  CachePolicy cache;  // of the population loads and stores (set_cache_policy)
+  int reverse;        // sweep from the last row to the first
   int occ_lds;  // dynamic LDS bytes reserved per workgroup (occupancy cap), 0: none
   // Intrinsic-force sub-steps run by extra workgroups of the same launch
   // (bond_groups > 0), each doing bond_nsub velocity-Verlet sub-steps of

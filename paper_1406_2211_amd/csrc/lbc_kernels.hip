@@ -85,7 +85,8 @@ __device__ __forceinline__ void take_forces_ib(uint64_t word, uint64_t* mp, size
 __device__ void bond_group(const BondArgs& b, int grp, int mode, int acc, int nsub, double dt,
                            double* lds);
 
-template <int S, bool CM, bool WALL, bool NS = false, bool MRT = false, bool SG = false>
+template <int S, bool CM, bool WALL, bool NS = false, bool MRT = false, bool SG = false,
+          int CP = kStream>
 __global__ __launch_bounds__(256) void k_stream_collide(LatArgs a) {
   using St = Store<S>;
   using T = typename St::T;
@@ -101,7 +102,11 @@ __global__ __launch_bounds__(256) void k_stream_collide(LatArgs a) {
   }
   const uint32_t nx = (uint32_t)a.g.nx, ny = (uint32_t)a.g.ny, nz = (uint32_t)a.g.nz;
   const uint32_t x = blockIdx.x * blockDim.x + threadIdx.x;
-  const uint32_t y = blockIdx.y, z = blockIdx.z - (a.bond_groups > 0 ? 1u : 0u);
+  uint32_t y = blockIdx.y, z = blockIdx.z - (a.bond_groups > 0 ? 1u : 0u);
+  if (a.reverse) {
+    y = ny - 1 - y;
+    z = nz - 1 - z;
+  }
   if (x >= nx) return;
   const uint32_t ys[3] = {y == 0 ? ny - 1 : y - 1, y, y == ny - 1 ? 0 : y + 1};
   const uint32_t zs[3] = {z == 0 ? nz - 1 : z - 1, z, z == nz - 1 ? 0 : z + 1};
@@ -124,7 +129,8 @@ __global__ __launch_bounds__(256) void k_stream_collide(LatArgs a) {
     }
     // non-temporal loads measured faster for the FP32 pass (256^3: 441 -> 432 us)
     // and slower for 16-bit storage and with thermal noise
-    f[i] = (S == LB_F32 && !NS) ? St::raw_nt(base + off) : St::raw(base + off);
+    constexpr bool nt = CP == kKeepWritten || (CP == kStream && S == LB_F32 && !NS);
+    f[i] = nt ? St::raw_nt(base + off) : St::raw(base + off);
   }
   R Fx = R(a.Fx), Fy = R(a.Fy), Fz = R(a.Fz);
   if (word) {
@@ -154,10 +160,10 @@ __global__ __launch_bounds__(256) void k_stream_collide(LatArgs a) {
       k.lg[c] = R(a.lg[c]);
       k.ag[c] = R(a.ag[c]);
     }
-    fused_site_mrt<S, NS>(f, Fx, Fy, Fz, k, (T*)a.fout, N, own);
+    fused_site_mrt<S, NS, CP>(f, Fx, Fy, Fz, k, (T*)a.fout, N, own);
   } else {
-    fused_site<S, CM, NS, SG>(f, Fx, Fy, Fz, k, (T*)a.fout, N, own, (R*)a.sigma, (size_t)a.g.N,
-                              R(a.sp));
+    fused_site<S, CM, NS, SG, CP>(f, Fx, Fy, Fz, k, (T*)a.fout, N, own, (R*)a.sigma,
+                                  (size_t)a.g.N, R(a.sp));
   }
 }
 
@@ -1097,19 +1103,39 @@ static dim3 lattice_grid(const Geo& g, dim3 b) {
     default: { constexpr int SS = LB_BF16; CALL; } break;           \
   }
 
-template <int S, bool CM, bool WALL, bool NS, bool MRT, bool SG>
+template <int S, bool CM, bool WALL, bool NS, bool MRT, bool SG, int CP>
 __global__ __launch_bounds__(256) void k_stream_collide_lin(LatArgs a);
 
-template <bool CM, bool WALL, bool NS = false, bool MRT = false, bool SG = false>
-static void launch_sc(int storage, const LatArgs& a, dim3 gr, dim3 b, hipStream_t st) {
+template <int S, bool CM, bool WALL, bool NS, bool MRT, bool SG, int CP>
+static void launch_sc_cp(const LatArgs& a, dim3 gr, dim3 b, hipStream_t st) {
   if (a.g.wpr == 0) {  // linear mask: x extent not a multiple of 64
     const unsigned nb = (unsigned)((a.g.N + 255) / 256) + (unsigned)a.bond_groups;
-    LBC_STORAGE_SWITCH(storage, (k_stream_collide_lin<SS, CM, WALL, NS, MRT, SG>
-                                 <<<nb, 256, a.occ_lds, st>>>(a)));
+    k_stream_collide_lin<S, CM, WALL, NS, MRT, SG, CP><<<nb, 256, a.occ_lds, st>>>(a);
   } else {
-    LBC_STORAGE_SWITCH(storage,
-                       (k_stream_collide<SS, CM, WALL, NS, MRT, SG><<<gr, b, a.occ_lds, st>>>(a)));
+    k_stream_collide<S, CM, WALL, NS, MRT, SG, CP><<<gr, b, a.occ_lds, st>>>(a);
   }
+}
+
+// The cache policies other than streaming exist for the passes that
+// set_cache_policy gives them to.
+template <bool CM, bool WALL, bool NS = false, bool MRT = false, bool SG = false>
+static void launch_sc(int storage, const LatArgs& a, dim3 gr, dim3 b, hipStream_t st) {
+  if constexpr (!CM && !SG) {
+    if (a.cache == kResident) {
+      LBC_STORAGE_SWITCH(storage, (launch_sc_cp<SS, CM, WALL, NS, MRT, SG, kResident>(a, gr, b, st)));
+      return;
+    }
+    if constexpr (!NS) {
+      if (a.cache == kKeepWritten) {
+        if (storage == LB_F64)
+          launch_sc_cp<LB_F64, CM, WALL, NS, MRT, SG, kKeepWritten>(a, gr, b, st);
+        else
+          launch_sc_cp<LB_F32, CM, WALL, NS, MRT, SG, kKeepWritten>(a, gr, b, st);
+        return;
+      }
+    }
+  }
+  LBC_STORAGE_SWITCH(storage, (launch_sc_cp<SS, CM, WALL, NS, MRT, SG, kStream>(a, gr, b, st)));
 }
 
 // BGK and the two-rate collision share one kernel (BGK: equal rates); the
@@ -1393,7 +1419,8 @@ struct SlotView {
   __device__ void mrt(PassK<R>&) const {}  // ... and use the two-rate collision
 };
 
-template <int S, bool CM, bool WALL, class V, bool NS = false, bool MRT = false, bool SG = false>
+template <int S, bool CM, bool WALL, class V, bool NS = false, bool MRT = false, bool SG = false,
+          int CP = kStream>
 __device__ __forceinline__ void linear_site(const V& v, uint32_t s) {
   using St = Store<S>;
   using T = typename St::T;
@@ -1418,7 +1445,7 @@ __device__ __forceinline__ void linear_site(const V& v, uint32_t s) {
     const T* src = fin + (size_t)i * P + off;
     if (WALL && ((CY[i] == 1 && y == 0) || (CY[i] == -1 && y == ny - 1)))
       src = fin + (size_t)OPP[i] * P + s;  // halfway bounce-back: opposite population, same site
-    f[i] = St::raw(src);
+    f[i] = CP == kKeepWritten ? St::raw_nt(src) : St::raw(src);
   }
   R Fx = R(v.F(0)), Fy = R(v.F(1)), Fz = R(v.F(2));
   if (word) {  // a 64-aligned group of 64 lanes owns this mask word
@@ -1440,14 +1467,14 @@ __device__ __forceinline__ void linear_site(const V& v, uint32_t s) {
   if (NS) v.noise(k);
   if (MRT) {
     v.mrt(k);
-    fused_site_mrt<S, NS>(f, Fx, Fy, Fz, k, (T*)v.fout(), P, s);
+    fused_site_mrt<S, NS, CP>(f, Fx, Fy, Fz, k, (T*)v.fout(), P, s);
   } else {
-    fused_site<S, CM, NS, SG>(f, Fx, Fy, Fz, k, (T*)v.fout(), P, s, (R*)v.sigma(), (size_t)g.N,
-                              R(v.sp()));
+    fused_site<S, CM, NS, SG, CP>(f, Fx, Fy, Fz, k, (T*)v.fout(), P, s, (R*)v.sigma(),
+                                  (size_t)g.N, R(v.sp()));
   }
 }
 
-template <int S, bool CM, bool WALL, bool NS, bool MRT, bool SG>
+template <int S, bool CM, bool WALL, bool NS, bool MRT, bool SG, int CP>
 __global__ __launch_bounds__(256) void k_stream_collide_lin(LatArgs a) {
   uint32_t b = blockIdx.x;
   if (a.bond_groups > 0) {  // the first bond_groups workgroups run the intrinsic-force sub-steps
@@ -1458,7 +1485,8 @@ __global__ __launch_bounds__(256) void k_stream_collide_lin(LatArgs a) {
     }
     b -= (uint32_t)a.bond_groups;
   }
-  linear_site<S, CM, WALL, LatView, NS, MRT, SG>(LatView{a}, b * 256u + threadIdx.x);
+  if (a.reverse) b = gridDim.x - (uint32_t)a.bond_groups - 1u - b;
+  linear_site<S, CM, WALL, LatView, NS, MRT, SG, CP>(LatView{a}, b * 256u + threadIdx.x);
 }
 
 // The slot table is read-only during the lattice pass (only k_ens_advance
