@@ -1,5 +1,5 @@
 // lbc_internal.h -- argument blocks and launchers shared by the host runtime
-// (lbc_api.hip) and the kernels (lbc_kernels.hip).
+// (lbc_api.hip) and the kernel files.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -261,7 +261,20 @@ struct EnsArgs {
 hipError_t launch_ens_step(int storage, int K, const EnsArgs& e, int lat_grid, int part_grid,
                            int det, hipStream_t st);
 
+// Workgroups of the row-mapped launches: one covers (part of) an x row.
+inline dim3 lattice_block(const Geo& g) {
+  int bx = ((g.nx + 63) / 64) * 64;
+  if (bx > 256) bx = 256;
+  return dim3(bx, 1, 1);
+}
+inline dim3 lattice_grid(const Geo& g, dim3 b) {
+  return dim3((g.nx + b.x - 1) / b.x, g.ny, g.nz);
+}
+
 hipError_t launch_stream_collide(int storage, bool comoving, const LatArgs& a, hipStream_t st);
+// The same for boxes on the linear-site pass (g.wpr == 0).
+hipError_t launch_stream_collide_lin(int storage, bool comoving, const LatArgs& a,
+                                     hipStream_t st);
 hipError_t launch_init(int storage, const InitArgs& a, hipStream_t st);
 hipError_t launch_moments(int storage, const SiteArgs& a, double* rho, double* u, hipStream_t st);
 // gp, gm: factors of the even and odd non-equilibrium parts (1, 1: the
