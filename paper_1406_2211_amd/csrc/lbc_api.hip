@@ -1291,6 +1291,7 @@ struct EnsHost {
   lb_ctx* ctx = nullptr;
   size_t off = 0, bytes = 0;
   int64_t target = 0;
+  int64_t start = 0;  // lb_ensemble::issued when the slot joined the work lists
 };
 
 constexpr int kGraphSteps = 8;
@@ -1317,6 +1318,7 @@ struct lb_ensemble {
   int part_items = 1024;  // particle work items, rounded up (an autotuner candidate)
   hipGraphExec_t exec[2] = {nullptr, nullptr};  // kGraphSteps steps, one step
   bool graphs_ok = false;
+  int64_t issued = 0;  // batched steps enqueued so far
   std::string err;
 };
 
@@ -1414,6 +1416,7 @@ static lb_status ens_refresh(lb_ensemble* e) {
       hs[i] = slot_from_ctx(h.ctx);
       hs[i].steps_target = h.target;
       h.fresh = false;
+      h.start = e->issued;
       h.ctx->running = true;
     }
     const long long nch = (h.ctx->geo.N + 255) / 256;
@@ -1622,8 +1625,14 @@ lb_status lb_ensemble_step(lb_ensemble* e, int64_t nsteps) {
   if (e->dirty && (s = ens_refresh(e)) != LB_OK) return s;
   if (!e->graphs_ok && (s = ens_build_graphs(e)) != LB_OK) return s;
   int64_t k = 0;
-  for (; k + kGraphSteps <= nsteps; k += kGraphSteps) EHIPCHK(e, hipGraphLaunch(e->exec[0], e->st));
-  for (; k < nsteps; ++k) EHIPCHK(e, hipGraphLaunch(e->exec[1], e->st));
+  for (; k + kGraphSteps <= nsteps; k += kGraphSteps) {
+    EHIPCHK(e, hipGraphLaunch(e->exec[0], e->st));
+    e->issued += kGraphSteps;
+  }
+  for (; k < nsteps; ++k) {
+    EHIPCHK(e, hipGraphLaunch(e->exec[1], e->st));
+    e->issued += 1;
+  }
   return LB_OK;
 }
 
@@ -1634,14 +1643,19 @@ lb_status lb_ensemble_query(lb_ensemble* e, int32_t slot, int64_t* steps_done, i
   EnsHost& h = e->slots[slot];
   int64_t sd = 0;
   if (!h.fresh) {
-    EnsSlot d;
     EHIPCHK(e, hipStreamSynchronize(e->st));
-    EHIPCHK(e, hipMemcpy(&d, e->d_slots + slot, sizeof(EnsSlot), hipMemcpyDeviceToHost));
-    h.ctx->cur = d.cur;
-    h.ctx->pend = d.pend;
-    h.ctx->steps = d.steps_done;
-    for (int k = 0; k < 3; ++k) h.ctx->uref[k] = d.uref[k];
-    sd = d.steps_done;
+    // A slot takes every batched step until its budget is spent, so its state
+    // follows from the steps enqueued, as k_ens_advance sets it on the device
+    // (the reference velocity by the same sequence of additions): no copy of
+    // the slot record, which cost a poll of 24 slots 0.4 ms.
+    lb_ctx* x = h.ctx;
+    sd = std::min(h.target, e->issued - h.start);
+    if (x->p.comoving)
+      for (int64_t t = x->steps; t < sd; ++t)
+        for (int k = 0; k < 3; ++k) x->uref[k] += x->p.body_force[k] / x->p.rho0;
+    x->cur = (x->cur + (int)((sd - x->steps) & 1)) & 1;
+    if (sd > 0) x->pend = 1;
+    x->steps = sd;
   }
   if (steps_done) *steps_done = sd;
   if (done) *done = sd >= h.target ? 1 : 0;
@@ -1683,8 +1697,10 @@ lb_status lb_ensemble_autotune(lb_ensemble* e, int32_t steps_per_candidate, int3
   for (int lg : lat_c)
     for (int pg : part_c) {
       EHIPCHK(e, hipEventRecord(t0, e->st));
-      for (int k = 0; k < steps_per_candidate; ++k)
+      for (int k = 0; k < steps_per_candidate; ++k) {
         EHIPCHK(e, launch_ens_step(e->storage, e->kernel, a, lg, pg, e->det, e->st));
+        e->issued += 1;
+      }
       EHIPCHK(e, hipEventRecord(t1, e->st));
       EHIPCHK(e, hipEventSynchronize(t1));
       float ms;

@@ -220,6 +220,17 @@ class Lattice:
         t = self.torch.as_tensor(t, dtype=self.torch.float64, device=self.device)
         return t.reshape(shape).contiguous()
 
+    def _inputs_ready(self, *given):
+        """Waits until the arrays given by the caller can be read from any
+        stream: for the whole device where one is a device tensor (the stream it
+        was made on is not known), else for the current stream, on which _f64
+        copied them (a wait for the device would also wait for work of others,
+        such as the copies of a server's results)."""
+        if any(isinstance(t, self.torch.Tensor) and t.is_cuda for t in given):
+            self.torch.cuda.synchronize(self.device)
+        else:
+            self.torch.cuda.current_stream(self.device).synchronize()
+
     def _call(self, name, *args):
         _check(getattr(load(), name)(self.ctx, *args), self.ctx)
 
@@ -227,7 +238,7 @@ class Lattice:
     def lb_init_fluid(self, rho=None, u=None):
         r = None if rho is None else self._f64(rho, self.shape)
         v = None if u is None else self._f64(u, (3,) + self.shape)
-        self.torch.cuda.synchronize(self.device)
+        self._inputs_ready(rho, u)
         self._call("lb_init_fluid", _ptr(r), _ptr(v))
         self._keep = (r, v)
 
@@ -236,7 +247,7 @@ class Lattice:
         n = p.shape[0]
         v = None if vel is None else self._f64(vel, (n, 3))
         m = None if mass is None else self._f64(mass, (n,))
-        self.torch.cuda.synchronize(self.device)
+        self._inputs_ready(pos, vel, mass)
         self._call("lb_set_particles", n, _ptr(p), _ptr(v), _ptr(m))
         self._keep_p = (p, v, m)
         self.np = n
