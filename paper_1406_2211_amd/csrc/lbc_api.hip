@@ -328,6 +328,9 @@ static BondArgs bond_args(const lb_ctx* c, double* pos) {
   b.fint = c->L.fint;
   b.k = c->bond_k;
   b.r0 = c->bond_r0;
+  b.rL[0] = 1.0 / c->geo.nx;
+  b.rL[1] = 1.0 / c->geo.ny;
+  b.rL[2] = 1.0 / c->geo.nz;
   b.type = c->bond_type;
   return b;
 }

@@ -759,24 +759,6 @@ __device__ __forceinline__ void fused_site_mrt(const typename Store<S>::R f[Q],
 }
 
 // ---------------------------------------------------------- delta functions
-// One-dimensional weights of a delta-function stencil (Appendix A kernels).
-// Returns the first node j0; weights for nodes j0 .. j0+K-1.
-template <typename T>
-__device__ __forceinline__ T phi_eval_t(int K, T r) {
-  const T a = fabs(r);
-  if (K == 2) return a < T(1) ? T(1) - a : T(0);
-  if (K == 3) {
-    if (a <= T(0.5)) return (T(1) + sqrt(T(1) - T(3) * r * r)) / T(3);
-    if (a <= T(1.5)) return (T(5) - T(3) * a - sqrt(fmax(T(0), T(6) * a - T(2) - T(3) * r * r))) / T(6);
-    return T(0);
-  }
-  if (a <= T(1)) return (T(3) - T(2) * a + sqrt(T(1) + T(4) * a - T(4) * r * r)) / T(8);
-  if (a <= T(2)) return (T(5) - T(2) * a - sqrt(fmax(T(0), T(-7) + T(12) * a - T(4) * r * r))) / T(8);
-  return T(0);
-}
-
-__device__ __forceinline__ double phi_eval(int K, double r) { return phi_eval_t<double>(K, r); }
-
 // floor(X) as an int for any X: the argument is first clamped to [-2^30, 2^30]
 // (a NaN becomes -2^30), so a non-finite or runaway position (an unstable run,
 // an over-stretched FENE bond) still maps to an in-range integer that the
@@ -791,16 +773,16 @@ __device__ __forceinline__ int first_node(double X) {
   return K == 3 ? safe_floor(X + 0.5) - 1 : (K == 2 ? safe_floor(X) : safe_floor(X) - 1);
 }
 
-__device__ __forceinline__ int stencil(int K, double X, double w[4]) {
-  const int j0 = K == 3 ? safe_floor(X + 0.5) - 1 : (K == 2 ? safe_floor(X) : safe_floor(X) - 1);
-#pragma unroll
-  for (int k = 0; k < 4; ++k) w[k] = k < K ? phi_eval(K, (double)(j0 + k) - X) : 0.0;
-  return j0;
-}
-
 __device__ __forceinline__ int wrap_idx(int j, int n) {
   int r = j % n;
   return r < 0 ? r + n : r;
+}
+
+// j mod n for a stencil node: one compare-and-add for a node within a box
+// length of the box, the division otherwise.
+__device__ __forceinline__ int wrap_near(int j, int n) {
+  const int r = j < 0 ? j + n : (j >= n ? j - n : j);
+  return (unsigned)r < (unsigned)n ? r : wrap_idx(j, n);
 }
 
 // x - L floor(x/L); for x in [-L, 2L) (every drift of less than a box length)
@@ -812,6 +794,37 @@ __device__ __forceinline__ double wrap_pos(double x, double L) {
   return x - L * floor(x / L);
 }
 
+// One axis of a K-point stencil (Appendix A kernels) in closed form: the
+// first node j0 and two parameters t, q from which each of the K weights
+// follows in two operations (the K = 4 and K = 3 weights share one square
+// root).  K = 4: t = X - floor(X), j0 = floor(X) - 1, q = sqrt(1 + 4t - 4t^2),
+//   weights (3 - 2t - q, 3 - 2t + q, 1 + 2t + q, 1 + 2t - q) / 8;
+// K = 3: t = X - round(X), j0 = round(X) - 1, q = sqrt(1 - 3t^2),
+//   weights ((2 - 3t - q) / 6, (1 + q) / 3, (2 + 3t - q) / 6);
+// K = 2: t = X - floor(X), j0 = floor(X), weights (1 - t, t).
+// These are the piecewise definitions evaluated at the node distances
+// -1 - t, -t, 1 - t, 2 - t (K = 4) and -1 - t, -t, 1 - t (K = 3, 2).  The
+// position is clamped as in safe_floor, so any X gives an in-range node.
+template <int K, typename W>
+__device__ __forceinline__ void stencil_t(double X, int& j0, W& t, W& q) {
+  const double f = floor(fmin(fmax(K == 3 ? X + 0.5 : X, -1073741824.0), 1073741824.0));
+  j0 = (int)f - (K == 2 ? 0 : 1);
+  t = (W)(X - f);
+  q = K == 4 ? sqrt(W(1) + W(4) * t - W(4) * t * t) : (K == 3 ? sqrt(W(1) - W(3) * t * t) : W(0));
+}
+template <int K, typename W>
+__device__ __forceinline__ W node_weight(int k, W t, W q) {
+  if (K == 4) {
+    const W a = k < 2 ? W(3) : W(1), b = k < 2 ? W(-2) : W(2), c = (k == 1 || k == 2) ? W(1) : W(-1);
+    return (a + b * t + c * q) * W(0.125);
+  }
+  if (K == 3) {
+    if (k == 1) return (W(1) + q) * (W(1) / W(3));
+    return (W(2) + (k == 0 ? W(-3) : W(3)) * t - q) * (W(1) / W(6));
+  }
+  return k == 0 ? W(1) - t : t;
+}
+
 // ------------------------------------------------------------- reductions
 // Lanes per particle for a K-point stencil: one lane per stencil node (K^3),
 // rounded up to a power of two that divides the wavefront.
@@ -820,22 +833,7 @@ struct Lanes {
   static constexpr int L = K == 2 ? 8 : (K == 3 ? 32 : 64);
 };
 
-// Sum over an aligned group of L lanes (butterfly; every lane gets the sum).
-template <int L, typename T>
-__device__ __forceinline__ T group_sum_t(T v) {
-#pragma unroll
-  for (int o = L / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-template <int L>
-__device__ __forceinline__ double group_sum(double v) {
-#pragma unroll
-  for (int o = L / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-// Sum over an aligned group of G = 4 or 16 lanes with DPP moves (every lane
+// Sum over an aligned group of G = 4, 8 or 16 lanes with DPP moves (every lane
 // gets the sum): pairs and quads by quad permutations, then the two quads of
 // each 8-lane half by a half-row mirror and the two halves by a row mirror.
 template <int ctrl>
@@ -851,13 +849,11 @@ __device__ __forceinline__ double dpp_add(double v) {
 }
 template <int G, typename T>
 __device__ __forceinline__ T group_sum_dpp(T v) {
-  static_assert(G == 4 || G == 16, "DPP group sums cover 4 or 16 lanes");
+  static_assert(G == 4 || G == 8 || G == 16, "DPP group sums cover 4, 8 or 16 lanes");
   v = dpp_add<0xB1>(v);  // quad_perm [1,0,3,2]
   v = dpp_add<0x4E>(v);  // quad_perm [2,3,0,1]
-  if (G == 16) {
-    v = dpp_add<0x141>(v);  // row_half_mirror
-    v = dpp_add<0x140>(v);  // row_mirror
-  }
+  if (G >= 8) v = dpp_add<0x141>(v);  // row_half_mirror
+  if (G == 16) v = dpp_add<0x140>(v);  // row_mirror
   return v;
 }
 
@@ -872,6 +868,16 @@ __device__ __forceinline__ double wave_sum_dpp(double v) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
   };
   return (lane_value(0) + lane_value(16)) + (lane_value(32) + lane_value(48));
+}
+
+// Sum over the L lanes of a particle (8, 32 or 64), every lane getting it.
+template <int L>
+__device__ __forceinline__ double group_sum(double v) {
+  static_assert(L == 8 || L == 32 || L == 64, "lane groups of the 2-, 3- and 4-point kernels");
+  if constexpr (L == 8) return group_sum_dpp<8, double>(v);
+  if constexpr (L == 64) return wave_sum_dpp(v);
+  v = group_sum_dpp<16, double>(v);
+  return v + __shfl_xor(v, 16, 64);
 }
 
 __device__ __forceinline__ double wave_sum(double v) {

@@ -42,14 +42,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == LB_F64
 
 // half 0: P^1/2 then the first coupling half (physical u, spread into FA);
 // half 1: the second coupling half (post-stream u, spread into FB), then P^1/2.
+// The slot table and the work list are read-only here, as in k_ens_lattice.
 template <int S, int K>
-__global__ __launch_bounds__(256) void k_ens_couple(EnsArgs e, int half) {
+__global__ __launch_bounds__(256) void k_ens_couple(const EnsSlot* __restrict__ slots,
+                                                    const int2* __restrict__ items,
+                                                    const int* __restrict__ nitems, int half) {
   using E = typename Store<S>::R;
   constexpr int L = Lanes<K>::L;
-  const int n = *e.npitems;
+  const int n = *nitems;
   for (int it = blockIdx.x; it < n; it += gridDim.x) {
-    const int2 w = e.pitems[it];
-    const EnsSlot& sl = e.slots[w.x];
+    const int2 w = items[it];
+    const EnsSlot& sl = slots[w.x];
     if (!ens_active(sl) || sl.coupling == LB_COUPLE_NONE) continue;
     const int lane = threadIdx.x % L;
     if ((long long)w.y + (threadIdx.x & ~63u) / L >= sl.np) continue;  // a whole wavefront
@@ -91,23 +94,16 @@ __global__ __launch_bounds__(256) void k_ens_couple(EnsArgs e, int half) {
     const double m = sl.mass[p];
     double rp, up[3];
     group_interp<S, K>(a, r, half == 0, lane, rp, up, p);
-    const double al = sl.gamma * hh / m, be = sl.gamma * hh / rp;
+    a.coupling = sl.coupling;
+    a.gamma = sl.gamma;
+    a.hh = hh;
+    a.kT = 0.0;
+    a.fext[0] = sl.fx;
+    a.fext[1] = sl.fy;
+    a.fext[2] = sl.fz;
+    const double Fi[3] = {0, 0, 0};
     double Fh[3];
-    if (sl.coupling == LB_COUPLE_FC) {
-      const double den = 1.0 + 0.5 * al + 0.5 * be;
-      const double fe[3] = {sl.fx, sl.fy, sl.fz};
-      for (int k = 0; k < 3; ++k) {
-        Fh[k] = -(sl.gamma * (v[k] - up[k]) - 0.5 * be * fe[k]) / den;
-        v[k] += hh / m * Fh[k];
-      }
-    } else {
-      const double sm = al + be;
-      for (int k = 0; k < 3; ++k) {
-        const double d = v[k] - up[k];
-        Fh[k] = -sl.gamma / sm * d;
-        v[k] = v[k] - al / sm * d;
-      }
-    }
+    couple_update(a, p, m, rp, up, Fi, v, Fh);
     const double Ff[3] = {-Fh[0], -Fh[1], -Fh[2]};
     if (sl.det_on) {  // stored; k_ens_spread_det spreads it (and drifts after half 1)
       if (live && lane == 0)
@@ -206,7 +202,8 @@ hipError_t launch_ens_step(int storage, int K, const EnsArgs& e, int lat_grid, i
     if (half == 1)
       LBC_STORAGE_SWITCH(storage, (k_ens_lattice<SS><<<lat_grid, 256, 0, st>>>(e.slots, e.litems,
                                                                               e.nlitems)));
-    LBC_KERNEL_SWITCH(K, LBC_STORAGE_SWITCH(storage, (k_ens_couple<SS, KK><<<part_grid, 256, 0, st>>>(e, half))));
+    LBC_KERNEL_SWITCH(K, LBC_STORAGE_SWITCH(storage, (k_ens_couple<SS, KK><<<part_grid, 256, 0, st>>>(
+                                e.slots, e.pitems, e.npitems, half))));
     if (det) {
       LBC_KERNEL_SWITCH(K, (k_ens_spread_det<KK><<<part_grid, 256, 0, st>>>(e, half)));
       LBC_STORAGE_SWITCH(storage, (k_ens_det_finalize<SS><<<lat_grid, 256, 0, st>>>(e, half)));

@@ -31,6 +31,7 @@ struct BondArgs {
   const double* mass;
   double* fint;
   double k, r0;
+  double rL[3];  // 1/nx, 1/ny, 1/nz
   int type;
 };
 

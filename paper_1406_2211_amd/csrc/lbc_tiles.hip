@@ -191,13 +191,6 @@ __device__ __forceinline__ bool stamped(double w, uint32_t st) {
   return __double_as_longlong(w) == (long long)st;
 }
 
-// j mod n for a stencil node: one compare-and-add for a node within a box
-// length of the box, the division otherwise.
-__device__ __forceinline__ int wrap_near(int j, int n) {
-  const int r = j < 0 ? j + n : (j >= n ? j - n : j);
-  return (unsigned)r < (unsigned)n ? r : wrap_idx(j, n);
-}
-
 // Mask words per wavefront of the velocity pass: on the c3 shells 8 words
 // (about 20 flagged sites per wavefront) took 19.8 us against 21.1 for 16,
 // and the step 0.198 ms against 0.200 (32 words: 0.212, 4 words: 0.199).
@@ -219,37 +212,6 @@ __global__ __launch_bounds__(256) void k_flag_vel(SiteArgs s, const uint64_t* __
     u.w = stamp_value(W(0), stamp);
     ((V4*)Uv)[site_index(s.g, x, y, z)] = u;
   });
-}
-
-// One axis of a K-point stencil (Appendix A kernels) in closed form: the
-// first node j0 and two parameters t, q from which each of the K weights
-// follows in two operations (the K = 4 and K = 3 weights share one square
-// root).  K = 4: t = X - floor(X), j0 = floor(X) - 1, q = sqrt(1 + 4t - 4t^2),
-//   weights (3 - 2t - q, 3 - 2t + q, 1 + 2t + q, 1 + 2t - q) / 8;
-// K = 3: t = X - round(X), j0 = round(X) - 1, q = sqrt(1 - 3t^2),
-//   weights ((2 - 3t - q) / 6, (1 + q) / 3, (2 + 3t - q) / 6);
-// K = 2: t = X - floor(X), j0 = floor(X), weights (1 - t, t).
-// These are the piecewise definitions evaluated at the node distances
-// -1 - t, -t, 1 - t, 2 - t (K = 4) and -1 - t, -t, 1 - t (K = 3, 2).  The
-// position is clamped as in safe_floor, so any X gives an in-range node.
-template <int K, typename W>
-__device__ __forceinline__ void stencil_t(double X, int& j0, W& t, W& q) {
-  const double f = floor(fmin(fmax(K == 3 ? X + 0.5 : X, -1073741824.0), 1073741824.0));
-  j0 = (int)f - (K == 2 ? 0 : 1);
-  t = (W)(X - f);
-  q = K == 4 ? sqrt(W(1) + W(4) * t - W(4) * t * t) : (K == 3 ? sqrt(W(1) - W(3) * t * t) : W(0));
-}
-template <int K, typename W>
-__device__ __forceinline__ W node_weight(int k, W t, W q) {
-  if (K == 4) {
-    const W a = k < 2 ? W(3) : W(1), b = k < 2 ? W(-2) : W(2), c = (k == 1 || k == 2) ? W(1) : W(-1);
-    return (a + b * t + c * q) * W(0.125);
-  }
-  if (K == 3) {
-    if (k == 1) return (W(1) + q) * (W(1) / W(3));
-    return (W(2) + (k == 0 ? W(-3) : W(3)) * t - q) * (W(1) / W(6));
-  }
-  return k == 0 ? W(1) - t : t;
 }
 
 // Lanes per marker: one per (x, y) column of stencil nodes, K rounded up to a
