@@ -248,6 +248,7 @@ static SiteArgs site_args(const lb_ctx* c) {
   s.g = c->geo;
   s.f = c->L.f[c->cur];
   s.FB = c->L.FB;
+  s.mask = c->L.mask;
   s.rho0 = c->p.rho0;
   s.pfx = c->pend * c->p.body_force[0];
   s.pfy = c->pend * c->p.body_force[1];

@@ -247,20 +247,17 @@ __device__ __forceinline__ void pull(const typename Store<S>::T* __restrict__ f,
   const int xm = x == 0 ? g.nx - 1 : x - 1, xp = x == g.nx - 1 ? 0 : x + 1;
   const int ym = y == 0 ? g.ny - 1 : y - 1, yp = y == g.ny - 1 ? 0 : y + 1;
   const int zm = z == 0 ? g.nz - 1 : z - 1, zp = z == g.nz - 1 ? 0 : z + 1;
-  const long long own = site_index(g, x, y, z);
+  // 32-bit site offsets (a box has fewer than 2^32 sites)
+  const uint32_t xs[3] = {(uint32_t)xm, (uint32_t)x, (uint32_t)xp};
+  const uint32_t ys[3] = {(uint32_t)ym, (uint32_t)y, (uint32_t)yp};
+  const uint32_t zs[3] = {(uint32_t)zm * g.ny, (uint32_t)z * g.ny, (uint32_t)zp * g.ny};
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
-    long long src;
-    const bool bb = g.wall && ((CY[i] == 1 && y == 0) || (CY[i] == -1 && y == g.ny - 1));
-    if (bb) {
-      src = (long long)OPP[i] * g.ps + own;
-    } else {
-      const int xs = CX[i] == 1 ? xm : (CX[i] == -1 ? xp : x);
-      const int ys = CY[i] == 1 ? ym : (CY[i] == -1 ? yp : y);
-      const int zs = CZ[i] == 1 ? zm : (CZ[i] == -1 ? zp : z);
-      src = (long long)i * g.ps + site_index(g, xs, ys, zs);
-    }
-    out[i] = Store<S>::ld(f + src, inv);
+    const typename Store<S>::T* src =
+        f + (size_t)i * g.ps + ((zs[1 - CZ[i]] + ys[1 - CY[i]]) * (uint32_t)g.nx + xs[1 - CX[i]]);
+    if (CY[i] != 0 && g.wall && y == (CY[i] == 1 ? 0 : g.ny - 1))
+      src = f + (size_t)OPP[i] * g.ps + ((zs[1] + ys[1]) * (uint32_t)g.nx + xs[1]);
+    out[i] = Store<S>::ld(src, inv);
   }
 }
 
@@ -270,6 +267,19 @@ template <int S>
 __device__ __forceinline__ void add_pending(const SiteArgs& a, long long s, double j[3]) {
   using V4 = typename Store<S>::V4;
   const V4 fb = ((const V4*)a.FB)[s];
+  j[0] += 0.5 * ((double)fb.x + a.pfx);
+  j[1] += 0.5 * ((double)fb.y + a.pfy);
+  j[2] += 0.5 * ((double)fb.z + a.pfz);
+}
+
+// The same where every site of the box is visited: FB is read at flagged sites
+// only (it is zero elsewhere), 16 B less per site for one bit.
+template <int S>
+__device__ __forceinline__ void add_pending_flagged(const SiteArgs& a, uint32_t s, double j[3]) {
+  using V4 = typename Store<S>::V4;
+  V4 fb;
+  fb.x = fb.y = fb.z = 0;
+  if ((a.mask[s >> 6] >> (s & 63)) & 1ull) fb = ((const V4*)a.FB)[s];
   j[0] += 0.5 * ((double)fb.x + a.pfx);
   j[1] += 0.5 * ((double)fb.y + a.pfy);
   j[2] += 0.5 * ((double)fb.z + a.pfz);
@@ -333,48 +343,6 @@ __device__ __forceinline__ void site_phys_r(const SiteArgs& a, int x, int y, int
     if (CZ[i]) j[2] += R(CZ[i]) * fl[i];
   }
   const V4 fb = ((const V4*)a.FB)[site_index(a.g, x, y, z)];
-  j[0] += R(0.5) * ((R)fb.x + (R)a.pfx);
-  j[1] += R(0.5) * ((R)fb.y + (R)a.pfy);
-  j[2] += R(0.5) * ((R)fb.z + (R)a.pfz);
-}
-
-// site_phys_r with the populations loaded one after another (a rolled loop):
-// the same operations in the same order, for a rarely taken path whose 19
-// loads in flight would otherwise set the register budget of a whole kernel.
-template <int S, typename R>
-__device__ __forceinline__ void site_phys_r_seq(const SiteArgs& a, int x, int y, int z, R& drho,
-                                                R j[3]) {
-  using St = Store<S>;
-  using V4 = typename St::V4;
-  const typename St::T* __restrict__ f = (const typename St::T*)a.f;
-  const Geo& g = a.g;
-  const int xm = x == 0 ? g.nx - 1 : x - 1, xp = x == g.nx - 1 ? 0 : x + 1;
-  const int ym = y == 0 ? g.ny - 1 : y - 1, yp = y == g.ny - 1 ? 0 : y + 1;
-  const int zm = z == 0 ? g.nz - 1 : z - 1, zp = z == g.nz - 1 ? 0 : z + 1;
-  const long long own = site_index(g, x, y, z);
-  const bool ref = a.uref[0] != 0.0 || a.uref[1] != 0.0 || a.uref[2] != 0.0;
-  drho = 0;
-  j[0] = j[1] = j[2] = 0;
-#pragma unroll 1
-  for (int i = 0; i < Q; ++i) {
-    long long src;
-    const bool bb = g.wall && ((CY[i] == 1 && y == 0) || (CY[i] == -1 && y == g.ny - 1));
-    if (bb) {
-      src = (long long)OPP[i] * g.ps + own;
-    } else {
-      const int xs = CX[i] == 1 ? xm : (CX[i] == -1 ? xp : x);
-      const int ys = CY[i] == 1 ? ym : (CY[i] == -1 ? yp : y);
-      const int zs = CZ[i] == 1 ? zm : (CZ[i] == -1 ? zp : z);
-      src = (long long)i * g.ps + site_index(g, xs, ys, zs);
-    }
-    R fl = St::ld(f + src, (R)a.inv);
-    if (ref) fl += eref<R>(i, (R)a.rho0, (R)a.uref[0], (R)a.uref[1], (R)a.uref[2]);
-    drho += fl;
-    if (CX[i]) j[0] += R(CX[i]) * fl;
-    if (CY[i]) j[1] += R(CY[i]) * fl;
-    if (CZ[i]) j[2] += R(CZ[i]) * fl;
-  }
-  const V4 fb = ((const V4*)a.FB)[own];
   j[0] += R(0.5) * ((R)fb.x + (R)a.pfx);
   j[1] += R(0.5) * ((R)fb.y + (R)a.pfy);
   j[2] += R(0.5) * ((R)fb.z + (R)a.pfz);

@@ -62,6 +62,7 @@ __global__ __launch_bounds__(256) void k_ens_couple(const EnsSlot* __restrict__ 
     a.s.g = sl.g;
     a.s.f = half == 0 ? sl.f[sl.cur] : sl.f[1 - sl.cur];
     a.s.FB = sl.FB;
+    a.s.mask = sl.mask;
     a.s.rho0 = sl.rho0;
     a.s.pfx = sl.pend * sl.fx;
     a.s.pfy = sl.pend * sl.fy;

@@ -103,6 +103,7 @@ struct SiteArgs {
   Geo g;
   const void* f;
   const void* FB;
+  const uint64_t* mask;  // every nonzero vector of FB lies at a flagged site
   double rho0;
   double pfx, pfy, pfz;  // pending body force (0 before the first step, F_ext after)
   float inv;

@@ -25,18 +25,17 @@ __global__ void k_init(InitArgs a) {
   const double usq = ux * ux + uy * uy + uz * uz;
   const double drho = rho - a.rho0;
   T* f = (T*)a.f;
+  const int xs[3] = {x == 0 ? a.g.nx - 1 : x - 1, x, x == a.g.nx - 1 ? 0 : x + 1};
+  const int ys[3] = {y == 0 ? a.g.ny - 1 : y - 1, y, y == a.g.ny - 1 ? 0 : y + 1};
+  const int zs[3] = {z == 0 ? a.g.nz - 1 : z - 1, z, z == a.g.nz - 1 ? 0 : z + 1};
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
     const double v = feq_dev<double>(i, drho, rho, ux, uy, uz, usq);
-    const int ys = y - CY[i];
-    long long dst;
-    if (a.g.wall && (ys < 0 || ys >= a.g.ny)) {
+    long long dst;  // x - c_i, or the opposite population of the same site beyond a wall
+    if (CY[i] != 0 && a.g.wall && y == (CY[i] == 1 ? 0 : a.g.ny - 1))
       dst = (long long)OPP[i] * a.g.ps + s;
-    } else {
-      dst = (long long)i * a.g.ps +
-            site_index(a.g, wrap_idx(x - CX[i], a.g.nx), wrap_idx(ys, a.g.ny),
-                       wrap_idx(z - CZ[i], a.g.nz));
-    }
+    else
+      dst = (long long)i * a.g.ps + site_index(a.g, xs[1 - CX[i]], ys[1 - CY[i]], zs[1 - CZ[i]]);
     St::st(f + dst, (R)v, (R)a.scale);
   }
 }
@@ -47,8 +46,9 @@ __global__ void k_moments(SiteArgs a, double* rho, double* u) {
   const int y = blockIdx.y, z = blockIdx.z;
   if (x >= a.g.nx) return;
   double fl[Q], drho, j[3];
-  site_phys<S>(a, x, y, z, fl, drho, j, true);
   const long long s = site_index(a.g, x, y, z);
+  site_phys<S>(a, x, y, z, fl, drho, j, false);
+  add_pending_flagged<S>(a, (uint32_t)s, j);
   const double r = a.rho0 + drho;
   if (rho) rho[s] = r;
   u[s] = j[0] / r;
@@ -67,9 +67,10 @@ __global__ void k_populations(SiteArgs a, double* out, double gp, double gm, int
   const int y = blockIdx.y, z = blockIdx.z;
   if (x >= a.g.nx) return;
   double fl[Q], drho, j[3], jb[3];
-  site_phys<S>(a, x, y, z, fl, drho, jb, false);
-  site_phys<S>(a, x, y, z, fl, drho, j, true);
   const long long s = site_index(a.g, x, y, z);
+  site_phys<S>(a, x, y, z, fl, drho, jb, false);
+  for (int c = 0; c < 3; ++c) j[c] = jb[c];
+  add_pending_flagged<S>(a, (uint32_t)s, j);
   const double r = a.rho0 + drho;
   const double ub[3] = {jb[0] / r, jb[1] / r, jb[2] / r}, up[3] = {j[0] / r, j[1] / r, j[2] / r};
   const double sb = ub[0] * ub[0] + ub[1] * ub[1] + ub[2] * ub[2];
@@ -152,11 +153,11 @@ __global__ __launch_bounds__(256) void k_totals_sites(SiteArgs a, double* partia
   double v[4] = {0, 0, 0, 0};
   const long long stride = (long long)gridDim.x * blockDim.x;
   for (long long s = (long long)blockIdx.x * blockDim.x + threadIdx.x; s < a.g.N; s += stride) {
-    const int x = (int)(s % a.g.nx);
-    const long long r = s / a.g.nx;
-    const int y = (int)(r % a.g.ny), z = (int)(r / a.g.ny);
+    const uint32_t r = (uint32_t)s / (uint32_t)a.g.nx, z = r / (uint32_t)a.g.ny;
+    const int x = (int)((uint32_t)s - r * (uint32_t)a.g.nx), y = (int)(r - z * (uint32_t)a.g.ny);
     double fl[Q], drho, j[3];
-    site_phys<S>(a, x, y, z, fl, drho, j, true);
+    site_phys<S>(a, x, y, (int)z, fl, drho, j, false);
+    add_pending_flagged<S>(a, (uint32_t)s, j);
     v[0] += drho;
     v[1] += j[0];
     v[2] += j[1];
