@@ -523,8 +523,8 @@ static lb_status lattice_pass(lb_ctx* c, int bond_nsub = 0, double bond_dt = 0.0
   a.omm = c->omm;
   a.scale = c->scale;
   a.inv = c->inv;
-  a.rnx = 1.0 / c->geo.nx;
-  a.rny = 1.0 / c->geo.ny;
+  a.mnx = div_magic(c->geo.nx);
+  a.mny = div_magic(c->geo.ny);
   a.clear_mask = c->steps % kMaskKeep == 0 ? 1 : 0;
   a.ib_copy = (c->p.coupling == LB_COUPLE_IB && c->np > 0) ? 1 : 0;
   a.noise = c->p.kT > 0.0 ? 1 : 0;
@@ -1321,6 +1321,7 @@ struct lb_ensemble {
   int lat_grid = 0, part_grid = 512;  // lattice: one block per item (ens_refresh)
   int part_items = 1024;  // particle work items, rounded up (an autotuner candidate)
   hipGraphExec_t exec[2] = {nullptr, nullptr};  // kGraphSteps steps, one step
+  bool big = false;  // some box has populations of 4 GiB or more
   bool graphs_ok = false;
   int64_t issued = 0;  // batched steps enqueued so far
   std::string err;
@@ -1357,8 +1358,8 @@ static EnsArgs ens_args(const lb_ensemble* e) {
 static EnsSlot slot_from_ctx(const lb_ctx* c) {
   EnsSlot s{};
   s.g = c->geo;
-  s.rnx = 1.0 / c->geo.nx;
-  s.rny = 1.0 / c->geo.ny;
+  s.mnx = div_magic(c->geo.nx);
+  s.mny = div_magic(c->geo.ny);
   s.f[0] = c->L.f[0];
   s.f[1] = c->L.f[1];
   s.FA = c->L.FA;
@@ -1408,6 +1409,7 @@ static lb_status ens_refresh(lb_ensemble* e) {
   EHIPCHK(e, hipStreamSynchronize(e->st));
   EHIPCHK(e, hipMemcpy(hs.data(), e->d_slots, hs.size() * sizeof(EnsSlot), hipMemcpyDeviceToHost));
   std::vector<int2> li, pi;
+  bool big = false;
   const int L = e->kernel == 2 ? 8 : (e->kernel == 3 ? 32 : 64);
   const int ppb = 256 / L;
   for (int i = 0; i < e->max_slots; ++i) {
@@ -1423,6 +1425,7 @@ static lb_status ens_refresh(lb_ensemble* e) {
       h.start = e->issued;
       h.ctx->running = true;
     }
+    big = big || big_box(h.ctx->geo, e->storage);
     const long long nch = (h.ctx->geo.N + 255) / 256;
     for (long long k = 0; k < nch; ++k) li.push_back(make_int2(i, (int)k));
     for (long long p = 0; p < h.ctx->np; p += ppb) pi.push_back(make_int2(i, (int)p));
@@ -1436,8 +1439,9 @@ static lb_status ens_refresh(lb_ensemble* e) {
   // up to 4096; workgroups beyond the count leave at once, and the captured
   // graphs are rebuilt only when that size grows or falls below half.
   const int cap = std::max(4096, ((int)li.size() + 4095) / 4096 * 4096);
-  if (cap > e->lat_grid || 2 * cap < e->lat_grid) {
+  if (cap > e->lat_grid || 2 * cap < e->lat_grid || big != e->big) {
     e->lat_grid = cap;
+    e->big = big;
     ens_drop_graphs(e);
   }
   e->part_items = std::max(1024, ((int)pi.size() + 1023) / 1024 * 1024);
@@ -1469,7 +1473,8 @@ static lb_status ens_build_graphs(lb_ensemble* e) {
     hipGraph_t graph;
     EHIPCHK(e, hipStreamBeginCapture(e->st, hipStreamCaptureModeThreadLocal));
     for (int k = 0; k < n; ++k) {
-      hipError_t r = launch_ens_step(e->storage, e->kernel, a, e->lat_grid, e->part_grid, e->det, e->st);
+      hipError_t r = launch_ens_step(e->storage, e->kernel, a, e->lat_grid, e->part_grid, e->det,
+                                     e->big, e->st);
       if (r != hipSuccess) {
         (void)hipStreamEndCapture(e->st, &graph);
         e->err = std::string("capture: ") + hipGetErrorString(r);
@@ -1702,7 +1707,7 @@ lb_status lb_ensemble_autotune(lb_ensemble* e, int32_t steps_per_candidate, int3
     for (int pg : part_c) {
       EHIPCHK(e, hipEventRecord(t0, e->st));
       for (int k = 0; k < steps_per_candidate; ++k) {
-        EHIPCHK(e, launch_ens_step(e->storage, e->kernel, a, lg, pg, e->det, e->st));
+        EHIPCHK(e, launch_ens_step(e->storage, e->kernel, a, lg, pg, e->det, e->big, e->st));
         e->issued += 1;
       }
       EHIPCHK(e, hipEventRecord(t1, e->st));

@@ -107,78 +107,104 @@ __device__ __forceinline__ R eref(int i, R rho0, R ux, R uy, R uz) {
 }
 
 // ------------------------------------------------------------------ storage
+// T: stored type, B: its bits (what memory operations move), R: compute type.
 template <int S>
 struct Store;
 template <>
 struct Store<LB_F64> {
   using T = double;
+  using B = double;
   using R = double;
   using V4 = double4;
-  static __device__ __forceinline__ R ld(const T* p, R) { return *p; }
-  static __device__ __forceinline__ R raw(const T* p) { return *p; }
-  // non-temporal load (the row-mapped pass reads each population once)
-  static __device__ __forceinline__ R raw_nt(const T* p) { return __builtin_nontemporal_load(p); }
-  // populations are written once per pass and not re-read by it: non-temporal
-  // (st_raw), unless the next pass finds them in the last-level cache (st_cached)
-  static __device__ __forceinline__ void st(T* p, R v, R) { __builtin_nontemporal_store(v, p); }
-  static __device__ __forceinline__ void st_raw(T* p, R v) { __builtin_nontemporal_store(v, p); }
-  static __device__ __forceinline__ void st_cached(T* p, R v) { *p = v; }
+  static __device__ __forceinline__ R from_bits(B b) { return b; }
+  static __device__ __forceinline__ B to_bits(R v) { return v; }
 };
 template <>
 struct Store<LB_F32> {
   using T = float;
+  using B = float;
   using R = float;
   using V4 = float4;
-  static __device__ __forceinline__ R ld(const T* p, R) { return *p; }
-  static __device__ __forceinline__ R raw(const T* p) { return *p; }
-  static __device__ __forceinline__ R raw_nt(const T* p) { return __builtin_nontemporal_load(p); }
-  static __device__ __forceinline__ void st(T* p, R v, R) { __builtin_nontemporal_store(v, p); }
-  static __device__ __forceinline__ void st_raw(T* p, R v) { __builtin_nontemporal_store(v, p); }
-  static __device__ __forceinline__ void st_cached(T* p, R v) { *p = v; }
+  static __device__ __forceinline__ R from_bits(B b) { return b; }
+  static __device__ __forceinline__ B to_bits(R v) { return v; }
 };
 template <>
 struct Store<LB_F16> {
   using T = __half;
+  using B = unsigned short;
   using R = float;
   using V4 = float4;
-  // stored value is scale * (f - w rho0); inv is 1/scale (a power of two)
-  static __device__ __forceinline__ R ld(const T* p, R inv) { return __half2float(*p) * inv; }
-  static __device__ __forceinline__ R raw(const T* p) { return __half2float(*p); }
-  static __device__ __forceinline__ R raw_nt(const T* p) {
-    return __half2float(__ushort_as_half(__builtin_nontemporal_load((const unsigned short*)p)));
-  }
-  static __device__ __forceinline__ void st(T* p, R v, R scale) { st_raw(p, v * scale); }
-  static __device__ __forceinline__ void st_raw(T* p, R v) {
-    __builtin_nontemporal_store(__half_as_ushort(__float2half_rn(v)), (unsigned short*)p);
-  }
-  static __device__ __forceinline__ void st_cached(T* p, R v) { *p = __float2half_rn(v); }
+  static __device__ __forceinline__ R from_bits(B b) { return __half2float(__ushort_as_half(b)); }
+  static __device__ __forceinline__ B to_bits(R v) { return __half_as_ushort(__float2half_rn(v)); }
 };
 template <>
 struct Store<LB_BF16> {
   using T = __hip_bfloat16;
+  using B = unsigned short;
   using R = float;
   using V4 = float4;
-  static __device__ __forceinline__ R ld(const T* p, R inv) { return __bfloat162float(*p) * inv; }
-  static __device__ __forceinline__ R raw(const T* p) { return __bfloat162float(*p); }
-  static __device__ __forceinline__ R raw_nt(const T* p) {
-    // bf16 is the top half of an FP32 word
-    return __uint_as_float((uint32_t)__builtin_nontemporal_load((const unsigned short*)p) << 16);
+  static __device__ __forceinline__ R from_bits(B b) {
+    return __uint_as_float((uint32_t)b << 16);  // bf16 is the top half of an FP32 word
   }
-  static __device__ __forceinline__ void st(T* p, R v, R scale) { st_raw(p, v * scale); }
-  static __device__ __forceinline__ void st_raw(T* p, R v) {
+  static __device__ __forceinline__ B to_bits(R v) {
     const __hip_bfloat16 b = __float2bfloat16(v);
-    __builtin_nontemporal_store(*(const unsigned short*)&b, (unsigned short*)p);
+    return *(const unsigned short*)&b;
   }
-  static __device__ __forceinline__ void st_cached(T* p, R v) { *p = __float2bfloat16(v); }
 };
 
-// Store of one new population under a cache policy of the pass.
-template <int S, int CP>
-__device__ __forceinline__ void st_pop(typename Store<S>::T* p, typename Store<S>::R v) {
-  if constexpr (CP == kStream)
-    Store<S>::st_raw(p, v);
+// The stored value is scale * (f - w rho0) in 16-bit storage; inv is 1/scale (a
+// power of two).
+template <int S>
+__device__ __forceinline__ typename Store<S>::R ld_scaled(const typename Store<S>::T* p,
+                                                          typename Store<S>::R inv) {
+  using St = Store<S>;
+  const typename St::R v = St::from_bits(*(const typename St::B*)p);
+  return (S == LB_F16 || S == LB_BF16) ? v * inv : v;
+}
+template <int S>
+__device__ __forceinline__ void st_scaled(typename Store<S>::T* p, typename Store<S>::R v,
+                                          typename Store<S>::R scale) {
+  using St = Store<S>;
+  if (S == LB_F16 || S == LB_BF16) v *= scale;
+  __builtin_nontemporal_store(St::to_bits(v), (typename St::B*)p);
+}
+
+// Population arrays in the lattice pass: a wavefront-uniform base in scalar
+// registers and a byte offset per lane.  The empty statement keeps the base a
+// scalar of its own; otherwise the compiler adds the lane's offset to one base
+// first and forms every other address with a 64-bit vector addition, about 60
+// instructions per site.  The global address space spares flat accesses where
+// the pointer was loaded from memory.
+template <typename B>
+using gptr = __attribute__((address_space(1))) B*;
+template <typename B>
+__device__ __forceinline__ gptr<B> uniform_base(const void* p, size_t byte) {
+  uint64_t q = (uint64_t)p + byte;
+  asm("" : "+s"(q));
+  return (gptr<B>)q;
+}
+template <typename B, typename Off>
+__device__ __forceinline__ gptr<B> at_bytes(gptr<B> base, Off byte) {
+  return (gptr<B>)((gptr<const char>)base + byte);
+}
+
+// Load of one population, once per pass (nt: non-temporal).
+template <int S, bool NT>
+__device__ __forceinline__ typename Store<S>::R ld_pop(gptr<const typename Store<S>::B> p) {
+  if constexpr (NT)
+    return Store<S>::from_bits(__builtin_nontemporal_load(p));
   else
-    Store<S>::st_cached(p, v);
+    return Store<S>::from_bits(*p);
+}
+// Store of one new population under a cache policy of the pass: populations
+// are written once per pass and not re-read by it, so non-temporal unless the
+// next pass finds them in the last-level cache.
+template <int S, int CP>
+__device__ __forceinline__ void st_pop(gptr<typename Store<S>::B> p, typename Store<S>::R v) {
+  if constexpr (CP == kStream)
+    __builtin_nontemporal_store(Store<S>::to_bits(v), p);
+  else
+    *p = Store<S>::to_bits(v);
 }
 
 __device__ __forceinline__ long long site_index(const Geo& g, int x, int y, int z) {
@@ -221,21 +247,23 @@ __device__ __forceinline__ void flag_site(uint64_t* mw, uint64_t bit) {
   if (!(*mw & bit)) atomicOr((unsigned long long*)mw, bit);
 }
 
-// Quotient and remainder of n / d for 32-bit n and d >= 1, with rd = 1/d
-// (double, rounded) from the host: n * rd is within 1e-6 of n / d, so its
-// truncation is the quotient or one off, and one correction step fixes it.
-__device__ __forceinline__ uint32_t div_rem(uint32_t n, uint32_t d, double rd, uint32_t& rem) {
-  uint32_t q = (uint32_t)((double)n * rd);
-  long long r = (long long)n - (long long)q * d;
-  if (r < 0) {
-    q -= 1;
-    r += d;
-  } else if (r >= (long long)d) {
+// Quotient and remainder of n / d for 32-bit n and d >= 1, with m =
+// div_magic(d) from the host: n m / 2^32 lies in (n/d - 1, n/d], so its floor is
+// the quotient or one less, and one correction step fixes it.
+__device__ __forceinline__ uint32_t div_rem(uint32_t n, uint32_t d, uint32_t m, uint32_t& rem) {
+  uint32_t q = (uint32_t)(((uint64_t)n * m) >> 32), r = n - q * d;
+  if (r >= d) {
     q += 1;
     r -= d;
   }
-  rem = (uint32_t)r;
+  rem = r;
   return q;
+}
+
+// A stored population in the compute type R of the caller.
+template <int S, typename R>
+__device__ __forceinline__ R pull_value(const typename Store<S>::T* p, R inv) {
+  return (R)ld_scaled<S>(p, (typename Store<S>::R)inv);
 }
 
 // Pull gather: fbar_i(x) = f*_i(x - c_i), periodic, or the reflected opposite
@@ -257,7 +285,7 @@ __device__ __forceinline__ void pull(const typename Store<S>::T* __restrict__ f,
         f + (size_t)i * g.ps + ((zs[1 - CZ[i]] + ys[1 - CY[i]]) * (uint32_t)g.nx + xs[1 - CX[i]]);
     if (CY[i] != 0 && g.wall && y == (CY[i] == 1 ? 0 : g.ny - 1))
       src = f + (size_t)OPP[i] * g.ps + ((zs[1] + ys[1]) * (uint32_t)g.nx + xs[1]);
-    out[i] = Store<S>::ld(src, inv);
+    out[i] = pull_value<S, R>(src, inv);
   }
 }
 
@@ -471,16 +499,21 @@ __host__ __device__ inline const float* pick_terms<float>(const double*, const f
 // so neither the loads nor the stores need the scale; the U terms are
 // per-pass constants (comoving_terms).
 // With NS the thermal noise of site_noise is added to every stored value.
-template <int S, bool CM, bool NS = false, bool SG = false, int CP = kStream>
+// The new populations go to fo + i P + ob bytes; own is the site index.
+template <int S, bool CM, bool NS = false, bool SG = false, int CP = kStream, typename Off>
 __device__ __forceinline__ void fused_site(const typename Store<S>::R f[Q], typename Store<S>::R Fx,
                                            typename Store<S>::R Fy, typename Store<S>::R Fz,
                                            const PassK<typename Store<S>::R>& k,
-                                           typename Store<S>::T* __restrict__ fo, size_t P,
-                                           size_t own,
+                                           void* __restrict__ fo, size_t P,
+                                           Off ob, size_t own,
                                            typename Store<S>::R* __restrict__ sgo = nullptr,
                                            size_t sN = 0, typename Store<S>::R sp = 0) {
   using St = Store<S>;
   using R = typename St::R;
+  asm("" : "+v"(ob));  // a value of this block, so that the stores extend it in place
+  auto pop = [&](int i) {
+    return at_bytes(uniform_base<typename St::B>(fo, (size_t)i * P * sizeof(typename St::B)), ob);
+  };
   R d = 0, jx = 0, jy = 0, jz = 0;
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
@@ -515,7 +548,7 @@ __device__ __forceinline__ void fused_site(const typename Store<S>::R f[Q], type
     }
     R v = eh + R(2) * k.hp * (f[0] - eb);
     if (NS) v += nz[0];
-    st_pop<S, CP>(fo + own, v);
+    st_pop<S, CP>(pop(0), v);
   }
 #pragma unroll
   for (int i = 1; i < Q; i += 2) {
@@ -548,8 +581,8 @@ __device__ __forceinline__ void fused_site(const typename Store<S>::R f[Q], type
       if (CX[i] && CZ[i]) pxz += R(CX[i] * CZ[i]) * s2;
       if (CY[i] && CZ[i]) pyz += R(CY[i] * CZ[i]) * s2;
     }
-    st_pop<S, CP>(fo + (size_t)i * P + own, vi);
-    st_pop<S, CP>(fo + (size_t)(i + 1) * P + own, vj);
+    st_pop<S, CP>(pop(i), vi);
+    st_pop<S, CP>(pop(i + 1), vj);
   }
   if (SG) {  // viscous stress of the state this pass started from (Eq. viscstress)
     const R pf = sp * k.inv;
@@ -613,15 +646,19 @@ constexpr double mrt_inv_b(int k) {
 // over the opposite pairs: even rows see n_i + n_j, odd rows n_i - n_j.  The
 // row coefficients are compile-time integers, so only their nonzero terms
 // are formed.
-template <int S, bool NS, int CP = kStream>
+template <int S, bool NS, int CP = kStream, typename Off>
 __device__ __forceinline__ void fused_site_mrt(const typename Store<S>::R f[Q],
                                                typename Store<S>::R Fx, typename Store<S>::R Fy,
                                                typename Store<S>::R Fz,
                                                const PassK<typename Store<S>::R>& k,
-                                               typename Store<S>::T* __restrict__ fo, size_t P,
-                                               size_t own) {
+                                               void* __restrict__ fo, size_t P,
+                                               Off ob, size_t own) {
   using St = Store<S>;
   using R = typename St::R;
+  asm("" : "+v"(ob));  // a value of this block, so that the stores extend it in place
+  auto pop = [&](int i) {
+    return at_bytes(uniform_base<typename St::B>(fo, (size_t)i * P * sizeof(typename St::B)), ob);
+  };
   R d = 0, jx = 0, jy = 0, jz = 0;
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
@@ -705,7 +742,7 @@ __device__ __forceinline__ void fused_site_mrt(const typename Store<S>::R f[Q],
 #pragma unroll
     for (int q = 4; q < Q; ++q)
       if (!mrt_odd(q) && mrt_row(q, 0) != 0) c += R(mrt_row(q, 0)) * D[q];
-    st_pop<S, CP>(fo + own, eh0 + n0 - wgt<R>(0) * c);
+    st_pop<S, CP>(pop(0), eh0 + n0 - wgt<R>(0) * c);
   }
 #pragma unroll
   for (int p = 0; p < 9; ++p) {
@@ -721,8 +758,8 @@ __device__ __forceinline__ void fused_site_mrt(const typename Store<S>::R f[Q],
         ce += R(c) * D[q];
     }
     const R w = wgt<R>(i);
-    st_pop<S, CP>(fo + (size_t)i * P + own, Eh[p] + Oh[p] + nI[p] - w * (ce + co));
-    st_pop<S, CP>(fo + (size_t)(i + 1) * P + own, Eh[p] - Oh[p] + nJ[p] - w * (ce - co));
+    st_pop<S, CP>(pop(i), Eh[p] + Oh[p] + nI[p] - w * (ce + co));
+    st_pop<S, CP>(pop(i + 1), Eh[p] - Oh[p] + nJ[p] - w * (ce - co));
   }
 }
 

@@ -19,12 +19,13 @@ __device__ __forceinline__ bool ens_active(const EnsSlot& s) {
 
 // The slot table is read-only during the lattice pass (only k_ens_advance
 // writes it); with restrict-qualified arguments its fields are scalar loads.
-template <int S, bool CM>
+template <int S, bool CM, bool BIG>
 __device__ __forceinline__ void ens_lattice_item(const EnsSlot& sl, uint32_t chunk) {
-  linear_site<S, CM, false>(SlotView{sl}, chunk * 256u + threadIdx.x);
+  linear_site<S, CM, false, SlotView, false, false, false, kStream, BIG>(
+      SlotView{sl}, chunk * 256u + threadIdx.x);
 }
 
-template <int S>
+template <int S, bool BIG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == LB_F64 ? 4 : 8))) void k_ens_lattice(const EnsSlot* __restrict__ slots,
                                                      const int2* __restrict__ items,
                                                      const int* __restrict__ nitems) {
@@ -34,9 +35,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S == LB_F64
     const EnsSlot& sl = slots[w.x];
     if (!ens_active(sl)) continue;
     if (sl.comoving)
-      ens_lattice_item<S, true>(sl, (uint32_t)w.y);
+      ens_lattice_item<S, true, BIG>(sl, (uint32_t)w.y);
     else
-      ens_lattice_item<S, false>(sl, (uint32_t)w.y);
+      ens_lattice_item<S, false, BIG>(sl, (uint32_t)w.y);
   }
 }
 
@@ -198,11 +199,16 @@ __global__ void k_ens_advance(EnsArgs e) {
 }
 
 hipError_t launch_ens_step(int storage, int K, const EnsArgs& e, int lat_grid, int part_grid,
-                           int det, hipStream_t st) {
+                           int det, bool big, hipStream_t st) {
   for (int half = 0; half < 2; ++half) {
-    if (half == 1)
-      LBC_STORAGE_SWITCH(storage, (k_ens_lattice<SS><<<lat_grid, 256, 0, st>>>(e.slots, e.litems,
-                                                                              e.nlitems)));
+    if (half == 1) {
+      if (big)
+        LBC_STORAGE_SWITCH(storage, (k_ens_lattice<SS, true><<<lat_grid, 256, 0, st>>>(
+                                        e.slots, e.litems, e.nlitems)))
+      else
+        LBC_STORAGE_SWITCH(storage, (k_ens_lattice<SS, false><<<lat_grid, 256, 0, st>>>(
+                                        e.slots, e.litems, e.nlitems)))
+    }
     LBC_KERNEL_SWITCH(K, LBC_STORAGE_SWITCH(storage, (k_ens_couple<SS, KK><<<part_grid, 256, 0, st>>>(
                                 e.slots, e.pitems, e.npitems, half))));
     if (det) {

@@ -19,6 +19,17 @@ struct Geo {
                  // every population array starts on a 256-byte boundary
 };
 
+// Whether the byte offsets inside a population array of this box need more
+// than 32 bits.
+inline bool big_box(const Geo& g, int storage) {
+  return (unsigned long long)g.N * (storage == LB_F64 ? 8 : (storage == LB_F32 ? 4 : 2)) > 0xffffffffull;
+}
+
+// floor(2^32 / d), the multiplier of div_rem (2^32 - 1 for d = 1).
+inline uint32_t div_magic(int d) {
+  return d <= 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (unsigned)d);
+}
+
 struct BondArgs {
   Geo g;
   const int32_t* perm;   // particles ordered by group
@@ -56,7 +67,7 @@ struct LatArgs {
   double uout[3];     // storage reference velocity of fout
   double cm[40];      // comoving reference terms of the pass (comoving_terms)
   float cmf[40];      // the same in FP32
-  double rnx, rny;    // 1/nx, 1/ny (linear-site pass)
+  uint32_t mnx, mny;  // div_magic of nx and ny (linear-site pass)
   int clear_mask;     // clear the force mask after reading it (every kMaskKeep steps)
   int ib_copy;        // immersed boundary: FA becomes the pending FB (same spread)
   // fluctuating collision (noise != 0): S sqrt(mu lambda (2 - lambda)) for the
@@ -222,7 +233,7 @@ hipError_t launch_tile_spread(int storage, int K, const TileArgs& t, const doubl
 // fields cur, pend and steps_done are advanced on the device only.
 struct EnsSlot {
   Geo g;  // wpr == 0: linear force mask
-  double rnx, rny;  // 1/nx, 1/ny for the site decomposition
+  uint32_t mnx, mny;  // div_magic of nx and ny for the site decomposition
   void* f[2];
   void* FA;
   void* FB;
@@ -260,8 +271,9 @@ struct EnsArgs {
 };
 
 // det: the deterministic spreading kernels run after each coupling half
+// big: some box has populations of 4 GiB or more
 hipError_t launch_ens_step(int storage, int K, const EnsArgs& e, int lat_grid, int part_grid,
-                           int det, hipStream_t st);
+                           int det, bool big, hipStream_t st);
 
 // Workgroups of the row-mapped launches: one covers (part of) an x row.
 inline dim3 lattice_block(const Geo& g) {

@@ -22,8 +22,9 @@ namespace lbc {
 // ======================================================================
 //
 // Addressing: a block covers (part of) one x row, so the y and z of the nine
-// source rows are block-uniform and live in scalar registers together with
-// the per-population base pointers; each work-item adds a 32-bit site offset.
+// source rows are block-uniform and the row pointers of every population live in
+// scalar registers; a work-item adds one of three 32-bit byte offsets (x - 1, x,
+// x + 1), without vector address arithmetic.
 // All 19 loads are issued before any arithmetic.  With y walls the
 // bounce-back choice is also block-uniform (it depends on y only).
 
@@ -55,24 +56,25 @@ __global__ __launch_bounds__(256) void k_stream_collide(LatArgs a) {
   const uint32_t xs[3] = {x == 0 ? nx - 1 : x - 1, x, x == nx - 1 ? 0 : x + 1};
   const uint32_t own = (z * ny + y) * nx + x;
   const size_t N = (size_t)a.g.ps;  // population stride
-  const T* __restrict__ fin = (const T*)a.fin;
   uint64_t* mp = a.mask + ((size_t)z * ny + y) * a.g.wpr + (x >> 6);
   const uint64_t word = *mp;
   R f[Q];
+  const uint32_t xb[3] = {xs[0] * (uint32_t)sizeof(T), x * (uint32_t)sizeof(T),
+                          xs[2] * (uint32_t)sizeof(T)};
+  const size_t row0 = ((size_t)z * ny + y) * nx;
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
     // source of population i: x - c_i
-    const uint32_t row = (zs[1 - CZ[i]] * ny + ys[1 - CY[i]]) * nx;
-    const T* base = fin + (size_t)i * N;
-    uint32_t off = row + xs[1 - CX[i]];
+    size_t base = (size_t)i * N + ((size_t)zs[1 - CZ[i]] * ny + ys[1 - CY[i]]) * nx;
+    uint32_t off = xb[1 - CX[i]];
     if (WALL && ((CY[i] == 1 && y == 0) || (CY[i] == -1 && y == ny - 1))) {
-      base = fin + (size_t)OPP[i] * N;  // halfway bounce-back: opposite population, same site
-      off = own;
+      base = (size_t)OPP[i] * N + row0;  // halfway bounce-back: opposite population, same site
+      off = xb[1];
     }
     // non-temporal loads measured faster for the FP32 pass (256^3: 441 -> 432 us)
     // and slower for 16-bit storage and with thermal noise
     constexpr bool nt = CP == kKeepWritten || (CP == kStream && S == LB_F32 && !NS);
-    f[i] = nt ? St::raw_nt(base + off) : St::raw(base + off);
+    f[i] = ld_pop<S, nt>(at_bytes(uniform_base<const typename St::B>(a.fin, base * sizeof(T)), off));
   }
   R Fx = R(a.Fx), Fy = R(a.Fy), Fz = R(a.Fz);
   if (word) {
@@ -102,9 +104,9 @@ __global__ __launch_bounds__(256) void k_stream_collide(LatArgs a) {
       k.lg[c] = R(a.lg[c]);
       k.ag[c] = R(a.ag[c]);
     }
-    fused_site_mrt<S, NS, CP>(f, Fx, Fy, Fz, k, (T*)a.fout, N, own);
+    fused_site_mrt<S, NS, CP>(f, Fx, Fy, Fz, k, (T*)a.fout + row0, N, xb[1], own);
   } else {
-    fused_site<S, CM, NS, SG, CP>(f, Fx, Fy, Fz, k, (T*)a.fout, N, own, (R*)a.sigma,
+    fused_site<S, CM, NS, SG, CP>(f, Fx, Fy, Fz, k, (T*)a.fout + row0, N, xb[1], own, (R*)a.sigma,
                                   (size_t)a.g.N, R(a.sp));
   }
 }

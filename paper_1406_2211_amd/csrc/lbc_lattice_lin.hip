@@ -5,7 +5,7 @@
 
 namespace lbc {
 
-template <int S, bool CM, bool WALL, bool NS, bool MRT, bool SG, int CP>
+template <int S, bool CM, bool WALL, bool NS, bool MRT, bool SG, int CP, bool BIG>
 __global__ __launch_bounds__(256) void k_stream_collide_lin(LatArgs a) {
   uint32_t b = blockIdx.x;
   if (a.bond_groups > 0) {  // the first bond_groups workgroups run the intrinsic-force sub-steps
@@ -17,17 +17,25 @@ __global__ __launch_bounds__(256) void k_stream_collide_lin(LatArgs a) {
     b -= (uint32_t)a.bond_groups;
   }
   if (a.reverse) b = gridDim.x - (uint32_t)a.bond_groups - 1u - b;
-  linear_site<S, CM, WALL, LatView, NS, MRT, SG, CP>(LatView{a}, b * 256u + threadIdx.x);
+  linear_site<S, CM, WALL, LatView, NS, MRT, SG, CP, BIG>(LatView{a}, b * 256u + threadIdx.x);
 }
 
 namespace {
 struct LinLaunch {
   const LatArgs& a;
   unsigned blocks;
+  bool big;
   hipStream_t st;
   template <int S, bool CM, bool WALL, bool NS, bool MRT, bool SG, int CP>
   void go() const {
-    k_stream_collide_lin<S, CM, WALL, NS, MRT, SG, CP><<<blocks, 256, a.occ_lds, st>>>(a);
+    if constexpr (CP == kStream) {  // (a box with a cache policy is far smaller)
+      if (big) {
+        k_stream_collide_lin<S, CM, WALL, NS, MRT, SG, CP, true>
+            <<<blocks, 256, a.occ_lds, st>>>(a);
+        return;
+      }
+    }
+    k_stream_collide_lin<S, CM, WALL, NS, MRT, SG, CP, false><<<blocks, 256, a.occ_lds, st>>>(a);
   }
 };
 }  // namespace
@@ -37,7 +45,7 @@ hipError_t launch_stream_collide_lin(int storage, bool comoving, const LatArgs& 
   // the bond groups run in bond_groups workgroups in front
   if (a.bond_groups > 0 && a.bond_cap > 256) return hipErrorInvalidValue;
   const unsigned nb = (unsigned)((a.g.N + 255) / 256) + (unsigned)a.bond_groups;
-  select_pass(storage, comoving, a, LinLaunch{a, nb, st});
+  select_pass(storage, comoving, a, LinLaunch{a, nb, big_box(a.g, storage), st});
   return hipGetLastError();
 }
 

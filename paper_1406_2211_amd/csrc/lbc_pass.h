@@ -3,6 +3,8 @@
 // choice of a pass variant.
 #pragma once
 
+#include <type_traits>
+
 #include "lbc_device.h"
 #include "lbc_internal.h"
 
@@ -73,8 +75,8 @@ __device__ __forceinline__ void take_forces_ib(uint64_t word, uint64_t* mp, size
 struct LatView {
   const LatArgs& a;
   __device__ const Geo& g() const { return a.g; }
-  __device__ double rnx() const { return a.rnx; }
-  __device__ double rny() const { return a.rny; }
+  __device__ uint32_t mnx() const { return a.mnx; }
+  __device__ uint32_t mny() const { return a.mny; }
   __device__ const void* fin() const { return a.fin; }
   __device__ void* fout() const { return a.fout; }
   __device__ void* FA() const { return a.FA; }
@@ -114,8 +116,8 @@ struct LatView {
 struct SlotView {
   const EnsSlot& s;
   __device__ const Geo& g() const { return s.g; }
-  __device__ double rnx() const { return s.rnx; }
-  __device__ double rny() const { return s.rny; }
+  __device__ uint32_t mnx() const { return s.mnx; }
+  __device__ uint32_t mny() const { return s.mny; }
   __device__ const void* fin() const { return s.f[s.cur]; }
   __device__ void* fout() const { return s.f[1 - s.cur]; }
   __device__ void* FA() const { return s.FA; }
@@ -143,7 +145,7 @@ struct SlotView {
 };
 
 template <int S, bool CM, bool WALL, class V, bool NS = false, bool MRT = false, bool SG = false,
-          int CP = kStream>
+          int CP = kStream, bool BIG = false>
 __device__ __forceinline__ void linear_site(const V& v, uint32_t s) {
   using St = Store<S>;
   using T = typename St::T;
@@ -152,23 +154,52 @@ __device__ __forceinline__ void linear_site(const V& v, uint32_t s) {
   if (s >= (uint32_t)g.N) return;
   const uint32_t nx = (uint32_t)g.nx, ny = (uint32_t)g.ny, nz = (uint32_t)g.nz;
   const size_t P = (size_t)g.ps;  // population stride
-  uint32_t x, y;
-  const uint32_t r = div_rem(s, nx, v.rnx(), x);
-  const uint32_t z = div_rem(r, ny, v.rny(), y);
-  const uint32_t xs[3] = {x == 0 ? nx - 1 : x - 1, x, x == nx - 1 ? 0 : x + 1};
-  const uint32_t ys[3] = {y == 0 ? ny - 1 : y - 1, y, y == ny - 1 ? 0 : y + 1};
-  const uint32_t zr[3] = {(z == 0 ? nz - 1 : z - 1) * ny, z * ny, (z == nz - 1 ? 0 : z + 1) * ny};
-  const T* __restrict__ fin = (const T*)v.fin();
+  // Coordinates: of the wavefront's first site by scalar arithmetic where a row
+  // holds a wavefront (its lanes then lie on two rows at most), else per lane.
+  uint32_t x, y, z;
+  if (nx >= 64) {
+    const uint32_t lane = s & 63u;
+    const uint32_t r = div_rem(__builtin_amdgcn_readfirstlane(s - lane), nx, v.mnx(), x);
+    z = div_rem(r, ny, v.mny(), y);
+    x += lane;
+    if (x >= nx) {
+      x -= nx;
+      if (++y == ny) {
+        y = 0;
+        ++z;
+      }
+    }
+  } else {
+    const uint32_t r = div_rem(s, nx, v.mnx(), x);
+    z = div_rem(r, ny, v.mny(), y);
+  }
   uint64_t* mp = v.mask() + (s >> 6);
   const uint64_t word = *mp;
   R f[Q];
+  // byte offsets inside a population array: 32 bits unless it is BIG (4 GiB or
+  // more); the neighbours' as periodic steps from the site's own, which wrap
+  // around in the offset type
+  using Off = std::conditional_t<BIG, size_t, uint32_t>;
+  const Off ob = (Off)s * (Off)sizeof(T);
+  const Off bx = sizeof(T), by = (Off)nx * bx, bz = (Off)ny * by;
+  const Off dx[3] = {x == 0 ? (Off)(nx - 1) * bx : (Off)0 - bx, 0,
+                     x == nx - 1 ? (Off)0 - (Off)(nx - 1) * bx : bx};
+  const Off dy[3] = {y == 0 ? (Off)(ny - 1) * by : (Off)0 - by, 0,
+                     y == ny - 1 ? (Off)0 - (Off)(ny - 1) * by : by};
+  const Off dz[3] = {z == 0 ? (Off)(nz - 1) * bz : (Off)0 - bz, 0,
+                     z == nz - 1 ? (Off)0 - (Off)(nz - 1) * bz : bz};
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
-    const uint32_t off = (zr[1 - CZ[i]] + ys[1 - CY[i]]) * nx + xs[1 - CX[i]];
-    const T* src = fin + (size_t)i * P + off;
-    if (WALL && ((CY[i] == 1 && y == 0) || (CY[i] == -1 && y == ny - 1)))
-      src = fin + (size_t)OPP[i] * P + s;  // halfway bounce-back: opposite population, same site
-    f[i] = CP == kKeepWritten ? St::raw_nt(src) : St::raw(src);
+    const Off off = ob + dx[1 - CX[i]] + dy[1 - CY[i]] + dz[1 - CZ[i]];
+    gptr<const typename St::B> src;
+    if (WALL && CY[i] != 0) {  // halfway bounce-back: opposite population, same site (per lane)
+      const bool bb = y == (CY[i] == 1 ? 0 : ny - 1);
+      src = at_bytes((gptr<const typename St::B>)(uint64_t)v.fin(),
+                     (size_t)(bb ? OPP[i] : i) * P * sizeof(T) + (bb ? ob : off));
+    } else {
+      src = at_bytes(uniform_base<const typename St::B>(v.fin(), (size_t)i * P * sizeof(T)), off);
+    }
+    f[i] = ld_pop<S, CP == kKeepWritten>(src);
   }
   R Fx = R(v.F(0)), Fy = R(v.F(1)), Fz = R(v.F(2));
   if (word) {  // a 64-aligned group of 64 lanes owns this mask word
@@ -190,9 +221,9 @@ __device__ __forceinline__ void linear_site(const V& v, uint32_t s) {
   if (NS) v.noise(k);
   if (MRT) {
     v.mrt(k);
-    fused_site_mrt<S, NS, CP>(f, Fx, Fy, Fz, k, (T*)v.fout(), P, s);
+    fused_site_mrt<S, NS, CP>(f, Fx, Fy, Fz, k, v.fout(), P, ob, s);
   } else {
-    fused_site<S, CM, NS, SG, CP>(f, Fx, Fy, Fz, k, (T*)v.fout(), P, s, (R*)v.sigma(),
+    fused_site<S, CM, NS, SG, CP>(f, Fx, Fy, Fz, k, v.fout(), P, ob, s, (R*)v.sigma(),
                                   (size_t)g.N, R(v.sp()));
   }
 }

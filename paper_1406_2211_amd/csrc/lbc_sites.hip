@@ -36,7 +36,7 @@ __global__ void k_init(InitArgs a) {
       dst = (long long)OPP[i] * a.g.ps + s;
     else
       dst = (long long)i * a.g.ps + site_index(a.g, xs[1 - CX[i]], ys[1 - CY[i]], zs[1 - CZ[i]]);
-    St::st(f + dst, (R)v, (R)a.scale);
+    st_scaled<S>(f + dst, (R)v, (R)a.scale);
   }
 }
 
