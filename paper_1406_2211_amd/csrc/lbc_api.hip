@@ -1128,10 +1128,7 @@ lb_status lb_stress_sweep(lb_ctx* c, void* d_sigma) {
 
 lb_status lb_get_particles(lb_ctx* c, double* d_pos, double* d_vel) {
   if (!c) return fail(nullptr, LB_EINVAL, "null context");
-  if (c->np > 0 && d_pos)
-    HIPCHK(c, hipMemcpyAsync(d_pos, c->L.pos, c->np * 24, hipMemcpyDeviceToDevice, c->st));
-  if (c->np > 0 && d_vel)
-    HIPCHK(c, hipMemcpyAsync(d_vel, c->L.vel, c->np * 24, hipMemcpyDeviceToDevice, c->st));
+  HIPCHK(c, launch_copy_particles(c->np, c->L.pos, c->L.vel, d_pos, d_vel, c->st));
   return LB_OK;
 }
 

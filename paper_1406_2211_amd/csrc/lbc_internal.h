@@ -304,6 +304,9 @@ hipError_t launch_totals(int storage, const SiteArgs& a, double* partial, int nb
 hipError_t launch_drift(const Geo& g, long long n, double* pos, const double* vel, double dt,
                         hipStream_t st);
 hipError_t launch_wrap(const Geo& g, long long n, double* pos, hipStream_t st);
+// Positions and velocities of n particles into d_pos and d_vel (either may be null).
+hipError_t launch_copy_particles(long long n, const double* pos, const double* vel, double* d_pos,
+                                 double* d_vel, hipStream_t st);
 // Zeroes bytes (a multiple of 8) at p with a fill kernel.
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t st);
 hipError_t launch_couple_half(int storage, const PartArgs& a, hipStream_t st);
