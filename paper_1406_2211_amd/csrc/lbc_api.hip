@@ -210,6 +210,7 @@ struct lb_ctx {
   bool flags_follow = false;  // tiled IB: the force mask holds the markers' last stencils
   bool member = false;  // slot of an ensemble: stepped only by lb_ensemble_step
   bool running = false;  // ensemble slot whose device record has been uploaded
+  bool first_done = false;  // the coming step's first coupling half is done (couple_second)
   bool mvalid = false;   // coupling moment cache holds the state of f[cur]
   int lds_cu = 0;        // LDS bytes per compute unit (for the lattice-pass occupancy cap)
   int nshell = 0, shell_size = 0;
@@ -258,7 +259,7 @@ static SiteArgs site_args(const lb_ctx* c) {
   return s;
 }
 
-static PartArgs part_args(const lb_ctx* c) {
+static PartArgs part_args(const lb_ctx* c, int64_t step) {
   PartArgs a;
   a.s = site_args(c);
   a.FA = c->L.FA;
@@ -286,8 +287,8 @@ static PartArgs part_args(const lb_ctx* c) {
   a.kT = c->p.coupling == LB_COUPLE_FC ? c->p.kT : 0.0;
   a.key0 = (uint32_t)c->p.seed;
   a.key1 = (uint32_t)(c->p.seed >> 32);
-  a.t0 = (uint32_t)c->steps;
-  a.t1 = (uint32_t)((uint64_t)c->steps >> 32);
+  a.t0 = (uint32_t)step;
+  a.t1 = (uint32_t)((uint64_t)step >> 32);
   a.jc = 0;
   a.hh = 0.5;
   a.hd = 0.5;
@@ -296,6 +297,8 @@ static PartArgs part_args(const lb_ctx* c) {
   a.defer = nullptr;
   return a;
 }
+
+static PartArgs part_args(const lb_ctx* c) { return part_args(c, c->steps); }
 
 static TileArgs tile_args(const lb_ctx* c) {
   TileArgs t;
@@ -659,6 +662,35 @@ static lb_status couple(lb_ctx* c, const PartArgs& a) {
   return LB_OK;
 }
 
+// The first coupling half of a step (FC, EBF; without intrinsic forces unless
+// use_fint), unless the previous step's couple_second did it.
+static PartArgs first_half(const lb_ctx* c, int64_t step, bool drift) {
+  PartArgs a = part_args(c, step);
+  a.target = 0;
+  a.drift_before = drift ? 1 : 0;
+  a.cache_use = c->mvalid ? 1 : 0;
+  return a;
+}
+static lb_status couple_first(lb_ctx* c, const PartArgs& a) {
+  if (c->first_done) {
+    c->first_done = false;
+    return LB_OK;
+  }
+  return couple(c, a);
+}
+
+// The second coupling half a of a step.  With another step to follow in this
+// call, no intrinsic forces between the halves and few enough particles, the
+// next step's first half (with the drift before it or not) runs in the same launch.
+static lb_status couple_second(lb_ctx* c, const PartArgs& a, bool more, bool drift) {
+  c->mvalid = true;
+  if (!more || a.use_fint || c->p.deterministic || !couple_pair_fits(c->np, c->p.kernel))
+    return couple(c, a);
+  HIPCHK(c, launch_couple_pair(c->p.storage, a, first_half(c, c->steps + 1, drift), c->st));
+  c->first_done = true;
+  return LB_OK;
+}
+
 // Deterministic spread of the intrinsic forces at the IB predictor positions
 // X~ (aux) into FA.
 static lb_status spread_fint_det(lb_ctx* c) {
@@ -773,7 +805,8 @@ static lb_status step_mts_inside_det(lb_ctx* c) {
   return LB_OK;
 }
 
-static lb_status step_once(lb_ctx* c) {
+// more: another step follows in this call.
+static lb_status step_once(lb_ctx* c, bool more) {
   const bool parts = c->p.coupling != LB_COUPLE_NONE && c->np > 0;
   lb_status s;
   if (!parts) {
@@ -837,10 +870,8 @@ static lb_status step_once(lb_ctx* c) {
   if (c->p.mts_substeps > 0) {
     const int n = c->p.mts_substeps;
     const double dt = 1.0 / (2.0 * n);
-    PartArgs a = part_args(c);
-    a.target = 0;
-    a.cache_use = c->mvalid ? 1 : 0;
-    if ((s = couple(c, a)) != LB_OK) return s;
+    PartArgs a = first_half(c, c->steps, false);
+    if ((s = couple_first(c, a)) != LB_OK) return s;
     // The 2n intrinsic-force sub-steps between the two coupling halves touch
     // only particle state and the lattice pass only fluid state, so all 2n
     // run together (bitwise the same as n, pass, n): as extra workgroups of
@@ -860,21 +891,16 @@ static lb_status step_once(lb_ctx* c) {
     a.target = 1;
     a.cache_fill = 1;
     a.jc = 1;
-    if ((s = couple(c, a)) != LB_OK) return s;
-    c->mvalid = true;
-    return LB_OK;
+    return couple_second(c, a, more, false);
   }
   // Alg. 3: P^1/2, F_int, coupling half (+ spread A), LB, coupling half (+ spread B), P^1/2.
   // Without intrinsic forces the first P^1/2 is done by the coupling kernel.
   const bool fint = c->nshell > 0 || c->nbond > 0;
   bool any = false;
   if (fint && (s = drift_and_fint(c, 0.5, any)) != LB_OK) return s;
-  PartArgs a = part_args(c);
+  PartArgs a = first_half(c, c->steps, !fint);
   a.use_fint = any ? 1 : 0;
-  a.drift_before = fint ? 0 : 1;
-  a.target = 0;
-  a.cache_use = c->mvalid ? 1 : 0;
-  if ((s = couple(c, a)) != LB_OK) return s;
+  if ((s = couple_first(c, a)) != LB_OK) return s;
   if ((s = lattice_pass(c)) != LB_OK) return s;
   a = part_args(c);
   a.use_fint = any ? 1 : 0;
@@ -883,9 +909,7 @@ static lb_status step_once(lb_ctx* c) {
   a.drift_after = 1;
   a.cache_fill = 1;
   a.jc = 1;
-  if ((s = couple(c, a)) != LB_OK) return s;
-  c->mvalid = true;
-  return LB_OK;
+  return couple_second(c, a, more && !fint, true);
 }
 
 extern "C" {
@@ -1084,8 +1108,9 @@ lb_status lb_step(lb_ctx* c, int64_t nsteps) {
     lb_status s = build_groups(c);
     if (s != LB_OK) return s;
   }
+  c->first_done = false;
   for (int64_t t = 0; t < nsteps; ++t) {
-    lb_status s = step_once(c);
+    lb_status s = step_once(c, t + 1 < nsteps);
     if (s != LB_OK) return s;
     c->steps++;
   }

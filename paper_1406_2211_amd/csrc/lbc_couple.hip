@@ -12,9 +12,20 @@ namespace lbc {
 // compute F^h over h' = a.hh (h/2 for the half steps of Alg. 3, h/2n for the
 // sub-steps of Eq. multistep), kick v, optionally drift, and spread -F^h
 // (scaled by a.sw) or store it for the deterministic spread.
+template <int S, int K, int WAVES>
+__device__ __forceinline__ void couple_spread(const PartArgs& a, const double r[3],
+                                              const double Ff[3], int lane, long long p, bool live,
+                                              uint64_t mpre) {
+  using E = typename Store<S>::R;
+  void* field = a.target ? a.FB : a.FA;
+  if constexpr (K == 2)
+    group_spread_k2<E, WAVES>(a, r, Ff, field, lane, p, live, mpre);
+  else
+    group_spread<E, K, WAVES>(a, r, Ff, field, lane, live, &mpre);
+}
+
 template <int S, int K>
 __global__ __launch_bounds__(256) void k_couple_half(PartArgs a) {
-  using E = typename Store<S>::R;
   constexpr int L = Lanes<K>::L;
   const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   const int lane = (int)(gid % L);
@@ -44,10 +55,7 @@ __global__ __launch_bounds__(256) void k_couple_half(PartArgs a) {
     if (live && lane == 0)
       for (int k = 0; k < 3; ++k) a.defer[3 * p + k] = Ff[k];
   } else {
-    if constexpr (K == 2)
-      group_spread_k2<E>(a, r, Ff, a.target ? a.FB : a.FA, lane, p, live, mpre);
-    else
-      group_spread<E, K>(a, r, Ff, a.target ? a.FB : a.FA, lane, live, &mpre);
+    couple_spread<S, K, 4>(a, r, Ff, lane, p, live, mpre);
   }
   if (live && lane == 0) {
     if (a.drift_after) {
@@ -58,6 +66,61 @@ __global__ __launch_bounds__(256) void k_couple_half(PartArgs a) {
       for (int k = 0; k < 3; ++k) a.pos[3 * p + k] = r[k];
     for (int k = 0; k < 3; ++k) a.vel[3 * p + k] = v[k];
   }
+}
+
+// The second coupling half of one step (a) and the first of the next (b) in one
+// launch of one workgroup, for particle sets that fit it: both see the same
+// populations, and the first half needs the forces that every particle spread
+// in the second, so between them only the workgroup has to meet.  The state and
+// the moments of the stencil nodes stay in registers.  Without intrinsic forces
+// in either half.  One particle at 32^3 (FP64): 5.8 + 5.2 -> 9.5 us a step.
+template <int S, int K>
+__global__ __launch_bounds__(kPairLanes) void k_couple_pair(PartArgs a, PartArgs b) {
+  constexpr int L = Lanes<K>::L, WAVES = kPairLanes / 64;
+  const int lane = (int)threadIdx.x % L;
+  const bool live = (int)threadIdx.x / L < a.n;
+  const bool wave = (int)(threadIdx.x & ~63u) / L < a.n;  // the wavefront holds a particle
+  const long long p = live ? threadIdx.x / L : a.n - 1;
+  double r[3], v[3], rp, up[3], Fh[3];
+  const double Fi[3] = {0, 0, 0};
+  for (int k = 0; k < 3; ++k) {
+    r[k] = a.pos[3 * p + k];
+    v[k] = a.vel[3 * p + k];
+  }
+  const double m = a.mass[p];
+  int4 base = make_int4(0, 0, 0, 0);
+  double4 mom = make_double4(0, 0, 0, 0);
+  if (wave) {
+    const uint64_t mpre = mask_preload<K>(a, r, lane);
+    group_interp<S, K>(a, r, false, lane, rp, up, p, nullptr, 0, nullptr, nullptr, &base, &mom);
+    couple_update(a, p, m, rp, up, Fi, v, Fh);
+    const double Ff[3] = {-Fh[0], -Fh[1], -Fh[2]};
+    couple_spread<S, K, WAVES>(a, r, Ff, lane, p, live, mpre);
+    if (a.drift_after) {
+      for (int k = 0; k < 3; ++k) r[k] += a.hd * v[k];
+      wrap3(a.s.g, r);
+    }
+    if (b.drift_before) {
+      for (int k = 0; k < 3; ++k) r[k] += b.hd * v[k];
+      wrap3(b.s.g, r);
+    }
+  }
+  // the spread forces are performed and seen by every wavefront (the float
+  // atomics go past the caches, so agent scope)
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  __syncthreads();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  if (!wave) return;
+  const uint64_t mpre = mask_preload<K>(b, r, lane);
+  group_interp<S, K>(b, r, true, lane, rp, up, p, nullptr, 0, &base, &mom);
+  couple_update(b, p, m, rp, up, Fi, v, Fh);
+  const double Ff[3] = {-Fh[0], -Fh[1], -Fh[2]};
+  couple_spread<S, K, WAVES>(b, r, Ff, lane, p, live, mpre);
+  if (live && lane == 0)
+    for (int k = 0; k < 3; ++k) {
+      if (a.drift_after || b.drift_before) b.pos[3 * p + k] = r[k];
+      b.vel[3 * p + k] = v[k];
+    }
 }
 
 // Adds W F of every particle (positions X, lattice forces F [n][3]) to the
@@ -268,6 +331,13 @@ hipError_t launch_couple_half(int storage, const PartArgs& a, hipStream_t st) {
   if (a.n > 0)
     LBC_KERNEL_SWITCH(a.K, LBC_STORAGE_SWITCH(storage, (k_couple_half<SS, KK>
                                                         <<<gblocks(a.n, KK), 256, 0, st>>>(a))));
+  return hipGetLastError();
+}
+
+hipError_t launch_couple_pair(int storage, const PartArgs& a, const PartArgs& b, hipStream_t st) {
+  if (a.n <= 0 || !couple_pair_fits(a.n, a.K)) return hipErrorInvalidValue;
+  const unsigned lanes = (unsigned)(a.n * (a.K == 2 ? 8 : (a.K == 3 ? 32 : 64)) + 63) / 64 * 64;
+  LBC_KERNEL_SWITCH(a.K, LBC_STORAGE_SWITCH(storage, (k_couple_pair<SS, KK><<<1, lanes, 0, st>>>(a, b))));
   return hipGetLastError();
 }
 

@@ -310,6 +310,16 @@ hipError_t launch_copy_particles(long long n, const double* pos, const double* v
 // Zeroes bytes (a multiple of 8) at p with a fill kernel.
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t st);
 hipError_t launch_couple_half(int storage, const PartArgs& a, hipStream_t st);
+// The second half a of one step and the first half b of the next by one
+// workgroup of at most one wavefront per SIMD of a CU; with more particles the
+// gathers and atomics of one CU take longer than the launch they save (64^3
+// FP32, 2-point, us per step as two launches -> as one: 1 particle 20.1 -> 18.9,
+// 32 particles 23.6 -> 22.6, 64 24.2 -> 27.6; 3-point, 16 particles 22.3 -> 23.1).
+constexpr int kPairLanes = 256;
+inline bool couple_pair_fits(long long n, int K) {
+  return n * (K == 2 ? 8 : (K == 3 ? 32 : 64)) <= kPairLanes;
+}
+hipError_t launch_couple_pair(int storage, const PartArgs& a, const PartArgs& b, hipStream_t st);
 // One coupled sub-step (SubArgs); and the fold: the nf fields u.gin moved
 // into the target field of a (a.target) at the flagged sites and left zero.
 hipError_t launch_mts_substep(int storage, const PartArgs& a, const SubArgs& u, hipStream_t st);

@@ -62,13 +62,16 @@ __device__ __forceinline__ SiteSlot slot_of(const Geo& g, const double X[3], int
 // the box stores its gathered moments, also at zero weight, so that a later
 // position with the same first node finds all of them; with a.cache_use and
 // an unchanged first node the cached moments replace the gather, and the
-// pending half force is added exactly as the gather would add it.
+// pending half force is added exactly as the gather would add it.  keep_base
+// and keep_m receive what a fill stores.
 template <int S, int K>
 __device__ __forceinline__ void group_interp(const PartArgs& a, const double X[3], bool phys,
                                              int lane, double& rp, double up[3], long long p,
                                              const void* const* gin = nullptr, int ngin = 0,
                                              const int4* pre_base = nullptr,
-                                             const double4* pre_m = nullptr) {
+                                             const double4* pre_m = nullptr,
+                                             int4* keep_base = nullptr,
+                                             double4* keep_m = nullptr) {
   constexpr int L = Lanes<K>::L;
   const SiteSlot sl = slot_of<K>(a.s.g, X, lane);
   const bool fill = a.cache_fill != 0 && !phys;
@@ -91,6 +94,7 @@ __device__ __forceinline__ void group_interp(const PartArgs& a, const double X[3
       double fl[Q];
       site_phys<S>(a.s, sl.x, sl.y, sl.z, fl, drho, j, phys);
       if (fill) a.mcache[p * L + lane] = make_double4(drho, j[0], j[1], j[2]);
+      if (keep_m) *keep_m = make_double4(drho, j[0], j[1], j[2]);
     }
     if (phys && a.fa_rd) add_field<S>(a.FA, site_index(a.s.g, sl.x, sl.y, sl.z), j);
     for (int f = 0; f < ngin; ++f) add_field<S>(gin[f], site_index(a.s.g, sl.x, sl.y, sl.z), j);
@@ -103,6 +107,7 @@ __device__ __forceinline__ void group_interp(const PartArgs& a, const double X[3
     }
   }
   if (fill && lane == 0) a.mbase[p] = make_int4(sl.j0[0], sl.j0[1], sl.j0[2], 0);
+  if (keep_base) *keep_base = make_int4(sl.j0[0], sl.j0[1], sl.j0[2], 0);
   rp = group_sum<L>(r);
   up[0] = group_sum<L>(ux);
   up[1] = group_sum<L>(uy);
@@ -137,9 +142,9 @@ struct AddSlot {
   E c[3];
   uint32_t site;
 };
-template <typename E>
+template <typename E, int WAVES>
 __device__ __forceinline__ void wave_add3(E* field, uint32_t sidx, E c0, E c1, E c2) {
-  __shared__ AddSlot<E> slots[4][64];  // workgroups of four wavefronts
+  __shared__ AddSlot<E> slots[WAVES][64];  // WAVES: wavefronts of the workgroup at most
   AddSlot<E>* w = slots[threadIdx.x >> 6];
   const int l = (int)threadIdx.x & 63;
   w[l] = AddSlot<E>{{c0, c1, c2}, sidx};
@@ -157,14 +162,14 @@ __device__ __forceinline__ void wave_add3(E* field, uint32_t sidx, E c0, E c1, E
 
 // Spread W F to the lane's stencil node; pre: the node's mask word from
 // mask_preload at the same X (nullptr: load it here).
-template <typename E, int K>
+template <typename E, int K, int WAVES = 4>
 __device__ __forceinline__ void group_spread(const PartArgs& a, const double X[3],
                                              const double F[3], void* field, int lane, bool live,
                                              const uint64_t* pre = nullptr) {
   const SiteSlot sl = slot_of<K>(a.s.g, X, lane);
   const bool on = live && sl.valid;
   const long long s = site_index(a.s.g, sl.x, sl.y, sl.z);
-  wave_add3<E>((E*)field, on ? (uint32_t)s : kNoSite, (E)(sl.W * F[0]), (E)(sl.W * F[1]),
+  wave_add3<E, WAVES>((E*)field, on ? (uint32_t)s : kNoSite, (E)(sl.W * F[0]), (E)(sl.W * F[1]),
                (E)(sl.W * F[2]));
   if (!on) return;
   uint64_t bit;
@@ -194,7 +199,7 @@ __device__ __forceinline__ void group_spread(const PartArgs& a, const double X[3
 // both lanes carry weight (a ballot).  Only the contributions themselves move
 // between lanes, one shuffle round per particle.  pre: the node's mask word
 // from mask_preload.
-template <typename E>
+template <typename E, int WAVES = 4>
 __device__ __forceinline__ void group_spread_k2(const PartArgs& a, const double X[3],
                                                 const double F[3], void* field, int lane,
                                                 long long p, bool live_p, uint64_t pre) {
@@ -234,7 +239,7 @@ __device__ __forceinline__ void group_spread_k2(const PartArgs& a, const double 
     }
     if (din && sidx >= 0 && ((live >> dst) & 1)) issue = false;  // handed on to particle i - 1
   }
-  wave_add3<E>((E*)field, issue ? (uint32_t)sidx : kNoSite, (E)c0, (E)c1, (E)c2);
+  wave_add3<E, WAVES>((E*)field, issue ? (uint32_t)sidx : kNoSite, (E)c0, (E)c1, (E)c2);
   if (!issue) return;
   uint64_t bit;
   uint64_t* mw = mask_word(a.mask, a.s.g, sl.x, sl.y, sl.z, bit);
