@@ -51,6 +51,8 @@ struct BondArgs {
 // loads and stores, kKeepWritten non-temporal loads and cached stores.
 enum CachePolicy { kStream = 0, kResident = 1, kKeepWritten = 2 };
 
+constexpr int kMtsFields = 4;  // sub-step fields held before a fold (SubArgs)
+
 // Fused lattice pass (stream, both pending half forces, collide).
 struct LatArgs {
   Geo g;
@@ -59,6 +61,8 @@ struct LatArgs {
   void* FA;         // first-half coupling force of this step (vec4 per site)
   void* FB;         // second-half coupling force of the previous step
   uint64_t* mask;   // per-site flag: FA or FB nonzero
+  void* G[kMtsFields];  // sub-step fields that join FA (step_mts_inside), ng of them
+  int ng;
   double rho0;
   double Fx, Fy, Fz;  // body force times the number of pending halves (1 or 2)
   double omp, omm;    // 1 - lambda for even / odd non-conserved moments
@@ -172,7 +176,6 @@ struct PartArgs {
 // field and the fields of the earlier sub-steps (gin): a sub-step never sees
 // its own spreads.  A fold launch moves those fields into the target field
 // at the flagged sites.
-constexpr int kMtsFields = 4;  // sub-step fields held before a fold
 constexpr int kSubPartners = 3;  // bond partners a sub-step holds in registers
 
 struct SubArgs {

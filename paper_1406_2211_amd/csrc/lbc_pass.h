@@ -11,11 +11,12 @@
 namespace lbc {
 
 // Coupling forces of one site for the fused pass, from the two force fields
-// where the mask word flags the site; both fields are zeroed after the read,
-// and the owning lane clears the word when the pass clears the mask.
+// where the mask word flags the site, and the ng sub-step fields that join FA;
+// the fields are zeroed after the read, and the owning lane clears the word when
+// the pass clears the mask.
 template <int S>
 __device__ __forceinline__ void take_forces(uint64_t word, uint64_t* mp, size_t site, uint32_t lane,
-                                            void* FAp, void* FBp, bool clear,
+                                            void* FAp, void* FBp, void* const* G, int ng, bool clear,
                                             typename Store<S>::R& Fx, typename Store<S>::R& Fy,
                                             typename Store<S>::R& Fz) {
   using V4 = typename Store<S>::V4;
@@ -30,6 +31,16 @@ __device__ __forceinline__ void take_forces(uint64_t word, uint64_t* mp, size_t 
     zero.x = zero.y = zero.z = zero.w = 0;
     FA[site] = zero;
     FB[site] = zero;
+    for (int k = 0; k < ng; ++k) {
+      V4* Gk = (V4*)G[k];
+      const V4 w = Gk[site];
+      if (w.x != 0 || w.y != 0 || w.z != 0) {
+        Fx += w.x;
+        Fy += w.y;
+        Fz += w.z;
+        Gk[site] = zero;
+      }
+    }
   }
   if (lane == 0 && clear) *mp = 0;
 }
@@ -81,6 +92,8 @@ struct LatView {
   __device__ void* fout() const { return a.fout; }
   __device__ void* FA() const { return a.FA; }
   __device__ void* FB() const { return a.FB; }
+  __device__ void* const* G() const { return a.G; }
+  __device__ int ng() const { return a.ng; }
   __device__ uint64_t* mask() const { return a.mask; }
   __device__ double F(int c) const { return c == 0 ? a.Fx : (c == 1 ? a.Fy : a.Fz); }
   __device__ double rho0() const { return a.rho0; }
@@ -122,6 +135,8 @@ struct SlotView {
   __device__ void* fout() const { return s.f[1 - s.cur]; }
   __device__ void* FA() const { return s.FA; }
   __device__ void* FB() const { return s.FB; }
+  __device__ void* const* G() const { return nullptr; }
+  __device__ int ng() const { return 0; }
   __device__ uint64_t* mask() const { return s.mask; }
   __device__ double F(int c) const {
     return (1 + s.pend) * (c == 0 ? s.fx : (c == 1 ? s.fy : s.fz));
@@ -206,7 +221,8 @@ __device__ __forceinline__ void linear_site(const V& v, uint32_t s) {
     if (v.ib_copy())
       take_forces_ib<S>(word, mp, s, s & 63, v.FA(), v.FB(), Fx, Fy, Fz);
     else
-      take_forces<S>(word, mp, s, s & 63, v.FA(), v.FB(), v.clear_mask(), Fx, Fy, Fz);
+      take_forces<S>(word, mp, s, s & 63, v.FA(), v.FB(), v.G(), v.ng(), v.clear_mask(), Fx, Fy,
+                     Fz);
   }
   PassK<R> k;
   k.rho0 = R(v.rho0());
