@@ -196,22 +196,51 @@ __device__ __forceinline__ bool stamped(double w, uint32_t st) {
 // and the step 0.198 ms against 0.200 (32 words: 0.212, 4 words: 0.199).
 constexpr int kVelWords = 8;
 
+// Physical velocity of one site into its stamped entry of the field U.
+template <int S>
+__device__ __forceinline__ void flag_vel_at(const SiteArgs& s, void* Uv, uint32_t stamp, int x,
+                                            int y, int z) {
+  using W = typename TileT<S>::W;
+  using V4 = typename Store<S>::V4;
+  W drho, j[3];
+  site_phys_r<S, W>(s, x, y, z, drho, j);
+  const W rr = W(s.rho0) + drho;
+  V4 u;
+  u.x = j[0] / rr;
+  u.y = j[1] / rr;
+  u.z = j[2] / rr;
+  u.w = stamp_value(W(0), stamp);
+  ((V4*)Uv)[site_index(s.g, x, y, z)] = u;
+}
+
 template <int S>
 __global__ __launch_bounds__(256) void k_flag_vel(SiteArgs s, const uint64_t* __restrict__ mask,
                                                   long long nwords, void* Uv, uint32_t stamp) {
-  using W = typename TileT<S>::W;
-  using V4 = typename Store<S>::V4;
   for_flagged_sites<kVelWords>(s.g, mask, nwords, [&](int x, int y, int z) {
-    W drho, j[3];
-    site_phys_r<S, W>(s, x, y, z, drho, j);
-    const W rr = W(s.rho0) + drho;
-    V4 u;
-    u.x = j[0] / rr;
-    u.y = j[1] / rr;
-    u.z = j[2] / rr;
-    u.w = stamp_value(W(0), stamp);
-    ((V4*)Uv)[site_index(s.g, x, y, z)] = u;
+    flag_vel_at<S>(s, Uv, stamp, x, y, z);
   });
+}
+
+// The same with a wavefront per mask word, each lane at its own bit: no scan and
+// no search before the gathers, which is what a small box waits on (four FP64
+// shells at 72 x 60 x 75, 5 063 words: 7.8 -> 4.3 us).  It takes as many
+// wavefronts as the box has words, flagged or not: the shell channel's 65 536
+// take as long as eight words per wavefront do (20.3 and 20.2 us), so larger
+// boxes keep those.
+constexpr long long kWordPerWave = 32768;  // mask words up to which it is used
+
+template <int S>
+__global__ __launch_bounds__(256) void k_flag_vel_word(SiteArgs s,
+                                                       const uint64_t* __restrict__ mask,
+                                                       long long nwords, void* Uv,
+                                                       uint32_t stamp) {
+  const long long w = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int bit = (int)threadIdx.x & 63;
+  if (w >= nwords || !((mask[w] >> bit) & 1ull)) return;
+  // (a row of 64-site words is also a run of 64-site linear words)
+  const uint32_t site = (uint32_t)(w * 64 + bit), nx = (uint32_t)s.g.nx, ny = (uint32_t)s.g.ny;
+  const uint32_t r = site / nx, z = r / ny;
+  flag_vel_at<S>(s, Uv, stamp, (int)(site - r * nx), (int)(r - z * ny), (int)z);
 }
 
 // Lanes per marker: one per (x, y) column of stencil nodes, K rounded up to a
@@ -382,11 +411,17 @@ __global__ __launch_bounds__(256) void k_marker_slow(SiteArgs s, const void* Uv,
 // 100 us).  The flags for the lattice pass are collected per region row in
 // LDS and set with one cached load and at most one atomic per mask word of
 // the row, instead of a dependent load per site.
+//
+// 512 lanes: the launch ends with its heaviest tiles (a 151-marker tile of the
+// shell channel), whose chain of staging, accumulation and flush 8 wavefronts
+// shorten (shell channel 32.9 -> 30.8 us, four FP64 shells 9.8 -> 8.6; 1024
+// lanes, two workgroups per CU: 32.9 and 8.6).
+constexpr int kSpreadLanes = 512;
 constexpr int kSpreadChunk = 128;  // markers staged per round
 constexpr int kRegRows = kReg * kReg;
 
 template <typename E, int K>
-__global__ __launch_bounds__(256) void k_tile_spread(TileArgs t, const double* at, const double* F,
+__global__ __launch_bounds__(kSpreadLanes) void k_tile_spread(TileArgs t, const double* at, const double* F,
                                                      void* field) {
   constexpr int KP = ColGroup<K>::KP, G = ColGroup<K>::G;
   extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -860,7 +895,11 @@ hipError_t launch_flag_interp(int storage, int K, const SiteArgs& s, const uint6
   // The listed markers are few once the flags follow the markers; right after
   // the fluid or the markers were set every marker is listed.
   const unsigned gs = all_miss ? gi : 64u;
-  LBC_TILE_S_SWITCH(storage, (k_flag_vel<SS><<<gv, 256, 0, st>>>(s, mask, nwords, U, stamp)));
+  if (nwords <= kWordPerWave)
+    LBC_TILE_S_SWITCH(storage, (k_flag_vel_word<SS><<<(unsigned)((nwords + 3) / 4), 256, 0, st>>>(
+                                   s, mask, nwords, U, stamp)))
+  else
+    LBC_TILE_S_SWITCH(storage, (k_flag_vel<SS><<<gv, 256, 0, st>>>(s, mask, nwords, U, stamp)))
   LBC_TILE_K_SWITCH(K, LBC_TILE_S_SWITCH(storage, (k_marker_interp<SS, KK><<<gi, 256, 0, st>>>(
                                                       s, U, stamp, at, pos, aux, mode, n, miss))));
   if (redo)
@@ -892,9 +931,9 @@ hipError_t launch_tile_spread(int storage, int K, const TileArgs& t, const doubl
   const size_t lds = sizeof(double) * (3 * kRegSites + 6 * kSpreadChunk) + 4 * kRegRows;
   const unsigned gr = tile_grid(t, 4);
   if (storage == LB_F64) {
-    LBC_TILE_K_SWITCH(K, (k_tile_spread<double, KK><<<gr, 256, lds, st>>>(t, at, F, field)));
+    LBC_TILE_K_SWITCH(K, (k_tile_spread<double, KK><<<gr, kSpreadLanes, lds, st>>>(t, at, F, field)));
   } else {
-    LBC_TILE_K_SWITCH(K, (k_tile_spread<float, KK><<<gr, 256, lds, st>>>(t, at, F, field)));
+    LBC_TILE_K_SWITCH(K, (k_tile_spread<float, KK><<<gr, kSpreadLanes, lds, st>>>(t, at, F, field)));
   }
   return hipGetLastError();
 }
