@@ -169,25 +169,9 @@ __device__ __forceinline__ void linear_site(const V& v, uint32_t s) {
   if (s >= (uint32_t)g.N) return;
   const uint32_t nx = (uint32_t)g.nx, ny = (uint32_t)g.ny, nz = (uint32_t)g.nz;
   const size_t P = (size_t)g.ps;  // population stride
-  // Coordinates: of the wavefront's first site by scalar arithmetic where a row
-  // holds a wavefront (its lanes then lie on two rows at most), else per lane.
-  uint32_t x, y, z;
-  if (nx >= 64) {
-    const uint32_t lane = s & 63u;
-    const uint32_t r = div_rem(__builtin_amdgcn_readfirstlane(s - lane), nx, v.mnx(), x);
-    z = div_rem(r, ny, v.mny(), y);
-    x += lane;
-    if (x >= nx) {
-      x -= nx;
-      if (++y == ny) {
-        y = 0;
-        ++z;
-      }
-    }
-  } else {
-    const uint32_t r = div_rem(s, nx, v.mnx(), x);
-    z = div_rem(r, ny, v.mny(), y);
-  }
+  uint32_t x, y;
+  const uint32_t r = div_rem(s, nx, v.mnx(), x);
+  const uint32_t z = div_rem(r, ny, v.mny(), y);
   uint64_t* mp = v.mask() + (s >> 6);
   const uint64_t word = *mp;
   R f[Q];
