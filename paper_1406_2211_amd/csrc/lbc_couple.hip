@@ -304,11 +304,16 @@ __global__ __launch_bounds__(256) void k_mts_substep(PartArgs a, SubArgs u) {
 // nonzero entry of a field lies on a site its spread flagged), one lane per
 // site: no two lanes share a site, so plain loads and stores suffice.  The
 // fields are left zero.
+//
+// Mask words per wavefront: 32 (1200 beads at 128^3: 6.5 us with 64, which leaves
+// half a wavefront per SIMD, 5.0 with 32, 16 or 8; 10^4 beads at 256^3: no difference).
+constexpr int kFoldWords = 32;
+
 template <int S>
 __global__ __launch_bounds__(256) void k_mts_fold(Geo g, const uint64_t* __restrict__ mask,
                                                   long long nwords, SubArgs u, int nf, void* T) {
   using V4 = typename Store<S>::V4;
-  for_flagged_sites<64>(g, mask, nwords, [&](int x, int y, int z) {
+  for_flagged_sites<kFoldWords>(g, mask, nwords, [&](int x, int y, int z) {
     const long long s = site_index(g, x, y, z);
     V4 t = ((const V4*)T)[s];
     bool any = false;
@@ -353,9 +358,9 @@ hipError_t launch_mts_fold(int storage, const PartArgs& a, const SubArgs& u, int
   if (nf <= 0) return hipSuccess;
   const Geo& g = a.s.g;
   const long long nwords = mask_nwords(g);
-  const long long per_wg = 4ll * 64;  // 64 words per wavefront: the mask is sparse here
-  const unsigned gr = (unsigned)std::min<long long>((nwords + per_wg - 1) / per_wg, 16384ll);
   void* T = a.target ? a.FB : a.FA;
+  const long long per_wg = 4ll * kFoldWords;
+  const unsigned gr = (unsigned)std::min<long long>((nwords + per_wg - 1) / per_wg, 16384ll);
   if (storage == LB_F64)
     k_mts_fold<LB_F64><<<gr, 256, 0, st>>>(g, a.mask, nwords, u, nf, T);
   else
