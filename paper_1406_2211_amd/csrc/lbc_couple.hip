@@ -14,12 +14,12 @@ namespace lbc {
 // (scaled by a.sw) or store it for the deterministic spread.
 template <int S, int K, int WAVES>
 __device__ __forceinline__ void couple_spread(const PartArgs& a, const double r[3],
-                                              const double Ff[3], int lane, long long p, bool live,
+                                              const double Ff[3], int lane, bool next, bool live,
                                               uint64_t mpre) {
   using E = typename Store<S>::R;
   void* field = a.target ? a.FB : a.FA;
   if constexpr (K == 2)
-    group_spread_k2<E, WAVES>(a, r, Ff, field, lane, p, live, mpre);
+    group_spread_k2<E, WAVES>(a, r, Ff, field, lane, next, live, mpre);
   else
     group_spread<E, K, WAVES>(a, r, Ff, field, lane, live, &mpre);
 }
@@ -27,13 +27,19 @@ __device__ __forceinline__ void couple_spread(const PartArgs& a, const double r[
 template <int S, int K>
 __global__ __launch_bounds__(256) void k_couple_half(PartArgs a) {
   constexpr int L = Lanes<K>::L;
-  const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  // With a spatial order each of the 8 XCDs (which take the workgroups in turn)
+  // gets a contiguous run of it, so that particles sharing lines of the
+  // populations share an L2.
+  const long long blk = a.order ? (long long)(blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3)
+                                : (long long)blockIdx.x;
+  const long long gid = blk * blockDim.x + threadIdx.x;
   const int lane = (int)(gid % L);
   if ((gid & ~63ll) / L >= a.n) return;  // whole wavefronts leave together
   // the lanes past the last particle follow it and write nothing (they serve
   // the wavefront's spreading)
   const bool live = gid / L < a.n;
-  const long long p = live ? gid / L : a.n - 1;
+  const long long slot = live ? gid / L : a.n - 1;
+  const long long p = a.order ? a.order[slot] : slot;
   double r[3], v[3], Fi[3] = {0, 0, 0};
   for (int k = 0; k < 3; ++k) {
     r[k] = a.pos[3 * p + k];
@@ -55,7 +61,7 @@ __global__ __launch_bounds__(256) void k_couple_half(PartArgs a) {
     if (live && lane == 0)
       for (int k = 0; k < 3; ++k) a.defer[3 * p + k] = Ff[k];
   } else {
-    couple_spread<S, K, 4>(a, r, Ff, lane, p, live, mpre);
+    couple_spread<S, K, 4>(a, r, Ff, lane, slot + 1 < a.n, live, mpre);
   }
   if (live && lane == 0) {
     if (a.drift_after) {
@@ -95,7 +101,7 @@ __global__ __launch_bounds__(kPairLanes) void k_couple_pair(PartArgs a, PartArgs
     group_interp<S, K>(a, r, false, lane, rp, up, p, nullptr, 0, nullptr, nullptr, &base, &mom);
     couple_update(a, p, m, rp, up, Fi, v, Fh);
     const double Ff[3] = {-Fh[0], -Fh[1], -Fh[2]};
-    couple_spread<S, K, WAVES>(a, r, Ff, lane, p, live, mpre);
+    couple_spread<S, K, WAVES>(a, r, Ff, lane, p + 1 < a.n, live, mpre);
     if (a.drift_after) {
       for (int k = 0; k < 3; ++k) r[k] += a.hd * v[k];
       wrap3(a.s.g, r);
@@ -115,7 +121,7 @@ __global__ __launch_bounds__(kPairLanes) void k_couple_pair(PartArgs a, PartArgs
   group_interp<S, K>(b, r, true, lane, rp, up, p, nullptr, 0, &base, &mom);
   couple_update(b, p, m, rp, up, Fi, v, Fh);
   const double Ff[3] = {-Fh[0], -Fh[1], -Fh[2]};
-  couple_spread<S, K, WAVES>(b, r, Ff, lane, p, live, mpre);
+  couple_spread<S, K, WAVES>(b, r, Ff, lane, p + 1 < a.n, live, mpre);
   if (live && lane == 0)
     for (int k = 0; k < 3; ++k) {
       if (a.drift_after || b.drift_before) b.pos[3 * p + k] = r[k];
@@ -287,7 +293,7 @@ __global__ __launch_bounds__(256) void k_mts_substep(PartArgs a, SubArgs u) {
   const double Ff[3] = {-a.sw * Fh[0], -a.sw * Fh[1], -a.sw * Fh[2]};
   void* field = u.gout ? u.gout : (a.target ? a.FB : a.FA);
   if constexpr (K == 2)
-    group_spread_k2<E>(a, r, Ff, field, lane, p, live, mpre);
+    group_spread_k2<E>(a, r, Ff, field, lane, p + 1 < a.n, live, mpre);
   else
     group_spread<E, K>(a, r, Ff, field, lane, live, &mpre);
   if (live && lane == 0) {
@@ -333,9 +339,11 @@ __global__ __launch_bounds__(256) void k_mts_fold(Geo g, const uint64_t* __restr
 }
 
 hipError_t launch_couple_half(int storage, const PartArgs& a, hipStream_t st) {
-  if (a.n > 0)
-    LBC_KERNEL_SWITCH(a.K, LBC_STORAGE_SWITCH(storage, (k_couple_half<SS, KK>
-                                                        <<<gblocks(a.n, KK), 256, 0, st>>>(a))));
+  if (a.n > 0) {
+    unsigned nb = gblocks(a.n, a.K);
+    if (a.order) nb = (nb + 7) / 8 * 8;
+    LBC_KERNEL_SWITCH(a.K, LBC_STORAGE_SWITCH(storage, (k_couple_half<SS, KK><<<nb, 256, 0, st>>>(a))));
+  }
   return hipGetLastError();
 }
 

@@ -155,6 +155,7 @@ struct PartArgs {
   double hd;         // length of drift_before / drift_after
   int fa_rd;         // the interpolated momentum also takes (h/2) FA (earlier sub-steps)
   double sw;         // scale of the lattice force written: 1, or 2 hh for sub-steps
+  const int* order;  // non-null: particles in the order to process them (spatial), else by index
   double* defer;     // non-null: store the lattice force per particle [n][3] here for a
                      // separate (deterministic) spread
   // Moment cache: the second coupling half stores, per particle and stencil

@@ -197,12 +197,12 @@ __device__ __forceinline__ void group_spread(const PartArgs& a, const double X[3
 // from lanes 8q into scalars): the predecessor's node k' is the successor's
 // node k' - d, d the difference of their first nodes, and a pair counts when
 // both lanes carry weight (a ballot).  Only the contributions themselves move
-// between lanes, one shuffle round per particle.  pre: the node's mask word
-// from mask_preload.
+// between lanes, one shuffle round per particle.  next: the launch has a particle
+// after this one; pre: the node's mask word from mask_preload.
 template <typename E, int WAVES = 4>
 __device__ __forceinline__ void group_spread_k2(const PartArgs& a, const double X[3],
                                                 const double F[3], void* field, int lane,
-                                                long long p, bool live_p, uint64_t pre) {
+                                                bool next, bool live_p, uint64_t pre) {
   const SiteSlot sl = slot_of<2>(a.s.g, X, lane);
   const bool on = live_p && sl.valid;
   const long long sidx = on ? site_index(a.s.g, sl.x, sl.y, sl.z) : -1;
@@ -210,7 +210,6 @@ __device__ __forceinline__ void group_spread_k2(const PartArgs& a, const double 
   const int wl = (int)(threadIdx.x & 63), qi = wl >> 3;
   const int kx = lane & 1, ky = (lane >> 1) & 1, kz = lane >> 2;
   const uint64_t live = __ballot(sidx >= 0);  // lanes that carry weight
-  const bool next = p + 1 < a.n;              // particle qi + 1 exists
   bool issue = sidx >= 0;
   int jx[8], jy[8], jz[8];  // first node of each particle of the wavefront
 #pragma unroll

@@ -34,3 +34,15 @@ def test_partial_wavefronts_fp64(kernel, n):
 def test_partial_wavefronts_fp32(kernel, coupling, storage, wall):
     c = _case(kernel, 35, coupling, storage, wall)
     compare(c, run_gpu(c), run_oracle(c), 1e-5)
+
+
+@pytest.mark.parametrize("kernel,n,box", [(2, 4100, (40, 36, 33)), (3, 4096, (33, 40, 36)), (4, 4353, (64, 24, 20))])
+def test_spatial_order(kernel, n, box):
+    """Dense free particles are processed in tile order, rebinned every 32 steps:
+    counts at the edges of the 8 equal runs of workgroups, across a rebinning."""
+    pos = I.uniform_positions(n, box, 7 + kernel)
+    vel = np.random.default_rng(n).normal(0.0, 2e-2, (n, 3))  # crosses tiles between binnings
+    c = Case(name=f"order_k{kernel}_n{n}", nx=box[0], ny=box[1], nz=box[2], tau=0.8, steps=35,
+             coupling=1, gamma=0.5, kernel=kernel, storage=0, u_noise=1e-3, pos=pos, vel=vel,
+             mass=np.full(n, 2.0), extra=dict(chunks=[33, 2]))
+    compare(c, run_gpu(c), run_oracle(c), 1e-12)
