@@ -47,8 +47,12 @@ __device__ __forceinline__ SiteSlot slot_of(const Geo& g, const double X[3], int
   } else {
     yy = wrap_near(yy, g.ny);
   }
-  s.W = node_weight<K, double>(kx, t[0], q[0]) * node_weight<K, double>(ky, t[1], q[1]) *
-        node_weight<K, double>(kz, t[2], q[2]);
+  // A position that is no number, or so far off that safe_floor clamps it, has no
+  // node within reach: no weight, so it neither reads nor forces the fluid (the
+  // closed forms would give NaN, or weights that grow with the distance).
+  if (fabs(t[0]) < 1.0 && fabs(t[1]) < 1.0 && fabs(t[2]) < 1.0)
+    s.W = node_weight<K, double>(kx, t[0], q[0]) * node_weight<K, double>(ky, t[1], q[1]) *
+          node_weight<K, double>(kz, t[2], q[2]);
   s.site = true;
   s.valid = s.W != 0.0;
   s.x = wrap_near(s.j0[0] + kx, g.nx);

@@ -46,3 +46,29 @@ def test_spatial_order(kernel, n, box):
              coupling=1, gamma=0.5, kernel=kernel, storage=0, u_noise=1e-3, pos=pos, vel=vel,
              mass=np.full(n, 2.0), extra=dict(chunks=[33, 2]))
     compare(c, run_gpu(c), run_oracle(c), 1e-12)
+
+
+@pytest.mark.parametrize("kernel,n,coupling,inside,free", [
+    (2, 12, 1, 0, 1), (2, 60, 2, 0, 1), (3, 20, 1, 0, 1), (4, 20, 2, 0, 1), (2, 60, 1, 1, 0)])
+def test_lost_particle(kernel, n, coupling, inside, free):
+    """A particle whose position is not a number (in one component or in all) neither
+    reads nor forces the fluid: fluid and other particles are those of the run without it."""
+    box = (20, 17, 19)
+    pos = I.uniform_positions(n, box, 3 + n)
+    vel = np.random.default_rng(n).normal(0.0, 1e-3, (n, 3))
+    mts = dict(mts=3, extra=dict(mts_inside=1)) if inside else {}
+    bonds = {} if free else dict(bonds=np.array([[0, 1], [2, 3]], np.int32), bond_k=1e-3, bond_r0=1.0)
+    runs = []
+    for lost in (0, 2):
+        p, v = pos.copy(), vel.copy()
+        if lost:
+            p = np.concatenate([p, [[np.nan] * 3, [3.2, np.nan, 4.1]]])
+            v = np.concatenate([v, np.zeros((2, 3))])
+        c = Case(name=f"lost{lost}_k{kernel}_n{n}_c{coupling}_i{inside}", nx=box[0], ny=box[1],
+                 nz=box[2], tau=0.8, steps=5, coupling=coupling, gamma=1.0, kernel=kernel,
+                 storage=0, u_noise=1e-3, pos=p, vel=v, mass=np.ones(n + lost), **bonds, **mts)
+        g = run_gpu(c)
+        runs.append((g["df"], g["u"], g["pos"][:n], g["vel"][:n]))
+    for a, b in zip(*runs):
+        assert np.isfinite(b).all()
+        assert np.abs(a - b).max() <= 1e-12 * np.abs(a).max()
