@@ -792,9 +792,9 @@ static lb_status step_mts_inside(lb_ctx* c) {
       HIPCHK(c, launch_mts_substep(c->p.storage, a, u, c->st));
       if (k > 0) ++used;
     }
-    // Before the pass, which visits every flagged site, the fields join FA there
+    // Before the row-mapped pass, which visits every flagged site, the fields join FA there
     // (one fold less per step: 1200 beads at 128^3, 6.4 us of 169).
-    if (side == 0)
+    if (side == 0 && c->geo.wpr != 0)
       joined = used;
     else if (used > 0)
       HIPCHK(c, launch_mts_fold(c->p.storage, a, u, used, c->st));

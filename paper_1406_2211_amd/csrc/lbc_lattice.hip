@@ -81,7 +81,7 @@ __global__ __launch_bounds__(256) void k_stream_collide(LatArgs a) {
     if (a.ib_copy)
       take_forces_ib<S>(word, mp, own, x & 63, a.FA, a.FB, Fx, Fy, Fz);
     else
-      take_forces<S>(word, mp, own, x & 63, a.FA, a.FB, a.G, a.ng, a.clear_mask != 0, Fx, Fy, Fz);
+      take_forces<S, true>(word, mp, own, x & 63, a.FA, a.FB, a.G, a.ng, a.clear_mask != 0, Fx, Fy, Fz);
   }
   PassK<R> k;
   k.rho0 = R(a.rho0);

@@ -11,10 +11,13 @@
 namespace lbc {
 
 // Coupling forces of one site for the fused pass, from the two force fields
-// where the mask word flags the site, and the ng sub-step fields that join FA;
-// the fields are zeroed after the read, and the owning lane clears the word when
-// the pass clears the mask.
-template <int S>
+// where the mask word flags the site, and with JOIN the ng sub-step fields that
+// join FA; the fields are zeroed after the read, and the owning lane clears the
+// word when the pass clears the mask.  FA's sum is complete before FB is added, as
+// after a fold.  Not in the linear-site pass: the loop there makes the
+// compiler contract another product of the equilibria, which rounds 16-bit
+// populations otherwise, also where no field joins.
+template <int S, bool JOIN>
 __device__ __forceinline__ void take_forces(uint64_t word, uint64_t* mp, size_t site, uint32_t lane,
                                             void* FAp, void* FBp, void* const* G, int ng, bool clear,
                                             typename Store<S>::R& Fx, typename Store<S>::R& Fy,
@@ -23,24 +26,25 @@ __device__ __forceinline__ void take_forces(uint64_t word, uint64_t* mp, size_t 
   if ((word >> lane) & 1ull) {
     V4* FA = (V4*)FAp;
     V4* FB = (V4*)FBp;
-    const V4 fa = FA[site], fb = FB[site];
-    Fx += fa.x + fb.x;
-    Fy += fa.y + fb.y;
-    Fz += fa.z + fb.z;
+    V4 fa = FA[site];
+    const V4 fb = FB[site];
     V4 zero;
     zero.x = zero.y = zero.z = zero.w = 0;
-    FA[site] = zero;
-    FB[site] = zero;
-    for (int k = 0; k < ng; ++k) {
+    for (int k = 0; JOIN && k < ng; ++k) {
       V4* Gk = (V4*)G[k];
       const V4 w = Gk[site];
       if (w.x != 0 || w.y != 0 || w.z != 0) {
-        Fx += w.x;
-        Fy += w.y;
-        Fz += w.z;
+        fa.x += w.x;
+        fa.y += w.y;
+        fa.z += w.z;
         Gk[site] = zero;
       }
     }
+    Fx += fa.x + fb.x;
+    Fy += fa.y + fb.y;
+    Fz += fa.z + fb.z;
+    FA[site] = zero;
+    FB[site] = zero;
   }
   if (lane == 0 && clear) *mp = 0;
 }
@@ -92,8 +96,6 @@ struct LatView {
   __device__ void* fout() const { return a.fout; }
   __device__ void* FA() const { return a.FA; }
   __device__ void* FB() const { return a.FB; }
-  __device__ void* const* G() const { return a.G; }
-  __device__ int ng() const { return a.ng; }
   __device__ uint64_t* mask() const { return a.mask; }
   __device__ double F(int c) const { return c == 0 ? a.Fx : (c == 1 ? a.Fy : a.Fz); }
   __device__ double rho0() const { return a.rho0; }
@@ -135,8 +137,6 @@ struct SlotView {
   __device__ void* fout() const { return s.f[1 - s.cur]; }
   __device__ void* FA() const { return s.FA; }
   __device__ void* FB() const { return s.FB; }
-  __device__ void* const* G() const { return nullptr; }
-  __device__ int ng() const { return 0; }
   __device__ uint64_t* mask() const { return s.mask; }
   __device__ double F(int c) const {
     return (1 + s.pend) * (c == 0 ? s.fx : (c == 1 ? s.fy : s.fz));
@@ -205,8 +205,7 @@ __device__ __forceinline__ void linear_site(const V& v, uint32_t s) {
     if (v.ib_copy())
       take_forces_ib<S>(word, mp, s, s & 63, v.FA(), v.FB(), Fx, Fy, Fz);
     else
-      take_forces<S>(word, mp, s, s & 63, v.FA(), v.FB(), v.G(), v.ng(), v.clear_mask(), Fx, Fy,
-                     Fz);
+      take_forces<S, false>(word, mp, s, s & 63, v.FA(), v.FB(), nullptr, 0, v.clear_mask(), Fx, Fy, Fz);
   }
   PassK<R> k;
   k.rho0 = R(v.rho0());
