@@ -645,20 +645,10 @@ static lb_status finish_step(lb_ctx* c) {
 }
 
 // Whether the coupling halves process the particles in tile order (binned every
-// kRebin steps; the order decides speed only).  A gather of one site takes whole
-// 128-byte lines of 19 populations, so free particles in index order fetch a
-// line for 8 useful bytes (20 000 at 128^3 FP32: 197 MB, 5.3 TB/s); in tile order
-// particles that share lines come together.  It pays from about one row of
-// stencil nodes per line of a population on (us per step, by index -> in order):
-// 2-point, 128^3, 20 000 particles, FP32 (1.2 rows per line) 113.5 -> 112.3, FP16
-// (2.4) 76.1 -> 66.5; 3-point, 10 000 (1.4) 125.4 -> 121.5; 4-point, 5 000 (1.2) 122.8
-// -> 119.4; 2-point, 10 000 (0.6) 93.2 -> 93.4, 200 x 150 x 130, 20 000 (0.7) 157.3 ->
-// 158.7.  Bonded beads are near their neighbours already.
+// kRebin steps).  Bonded beads are near their neighbours already.
 static bool spatial_order(const lb_ctx* c) {
-  const int K = c->p.kernel;
-  const double rows = (double)c->np * K * K;
-  const double lines = (double)c->geo.N * storage_bytes(c->p.storage) / 128.0;
-  return c->nbond == 0 && c->np >= 4096 && rows >= lines;
+  return c->nbond == 0 &&
+         order_pays(storage_bytes(c->p.storage), c->p.kernel, c->np, c->geo.N);
 }
 
 // One coupling step (k_couple_half).  In the deterministic mode the kernel

@@ -314,6 +314,26 @@ hipError_t launch_copy_particles(long long n, const double* pos, const double* v
 // Zeroes bytes (a multiple of 8) at p with a fill kernel.
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t st);
 hipError_t launch_couple_half(int storage, const PartArgs& a, hipStream_t st);
+// Whether np free particles of a box of N sites are processed in tile order
+// (PartArgs::order).  A gather of one site takes whole 128-byte lines of 19
+// populations, so particles in index order fetch a line for 8 useful bytes
+// (20 000 at 128^3 FP32: 197 MB, 5.3 TB/s); in tile order particles that share
+// lines come together.  It pays from about one row of stencil nodes per line of a
+// population on (us per step, by index -> in order): 2-point, 128^3, 20 000
+// particles, FP32 (1.2 rows per line) 113.5 -> 112.3; 3-point, 10 000 (1.4) 125.4
+// -> 121.5; 4-point, 5 000 (1.2) 122.8 -> 119.4; 2-point, 10 000 (0.6) 93.2 ->
+// 93.4, 200 x 150 x 130, 20 000 (0.7) 157.3 -> 158.7.
+// Not with 16-bit storage, though it would pay most there (FP16, 2.4 rows per
+// line, 76.1 -> 66.5).  By index the contributions of a site arrive in nearly the
+// same order in every run; in tile order they arrive in another one, and where
+// three or more meet, the last bit of their FP32 sum now and then moves a stored
+// 16-bit population by a quantum (80 x 180 x 147 FP16, 13 694 particles, 10 steps:
+// 36 of 36 pairs of runs, one in tile order and one by index, differ at single
+// sites by 1.3e-3 of the stress's rms; 15 of 15 pairs by index agree to 6e-8).
+inline bool order_pays(int storage_bytes, int K, long long np, long long N) {
+  const double rows = (double)np * K * K, lines = (double)N * storage_bytes / 128.0;
+  return storage_bytes >= 4 && np >= 4096 && rows >= lines;
+}
 // The second half a of one step and the first half b of the next by one
 // workgroup of at most one wavefront per SIMD of a CU; with more particles the
 // gathers and atomics of one CU take longer than the launch they save (64^3

@@ -1,0 +1,39 @@
+"""The host-side rules of the kernels' header, compiled for the CPU."""
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+SOURCE = r"""
+#include "lbc_internal.h"
+using namespace lbc;
+extern "C" int order_pays_c(int sb, int K, long long np, long long N) { return order_pays(sb, K, np, N); }
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "rules.hip").write_text(SOURCE)
+    lib = str(d / "rules.so")
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-host-only", "-O1", "-std=c++17",
+                    "-fPIC", "-shared", "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(ROOT, "paper_1406_2211_amd", "csrc"), str(d / "rules.hip"), "-o", lib],
+                   check=True)
+    return C.CDLL(lib)
+
+
+@pytest.mark.parametrize("K", [2, 3, 4])
+def test_tile_order_is_not_taken_by_16_bit_boxes(rules, K):
+    """Dense free particles are processed in tile order, except on 16-bit
+    storage, whose populations a changed order of the sums moves by a quantum."""
+    f = rules.order_pays_c
+    f.argtypes = [C.c_int, C.c_int, C.c_longlong, C.c_longlong]
+    for n, N in ((4096, 4096), (13694, 80 * 180 * 147), (1 << 20, 1 << 20)):
+        assert not f(2, K, n, N)
+    for sb in (4, 8):
+        N = 4096 * K * K * 128 // sb  # one row of nodes per line
+        assert f(sb, K, 4096, N) and not f(sb, K, 4095, N) and not f(sb, K, 4096, N + 128)
