@@ -33,6 +33,14 @@ struct SiteSlot {
   int j0[3];    // first stencil node, unwrapped
 };
 
+// Whether t of stencil_t is that of a position near its first node: [0, 1], or
+// [-1/2, 1/2] and the rounding of X + 1/2 for the 3-point kernel (whose square root
+// exists up to 0.577).
+template <int K>
+__device__ __forceinline__ bool in_reach(double t) {
+  return K == 3 ? fabs(t) <= 0.5625 : (t >= 0.0 && t <= 1.0);
+}
+
 template <int K>
 __device__ __forceinline__ SiteSlot slot_of(const Geo& g, const double X[3], int lane) {
   SiteSlot s{false, false, 0.0, 0, 0, 0, {0, 0, 0}};
@@ -49,8 +57,10 @@ __device__ __forceinline__ SiteSlot slot_of(const Geo& g, const double X[3], int
   }
   // A position that is no number, or so far off that safe_floor clamps it, has no
   // node within reach: no weight, so it neither reads nor forces the fluid (the
-  // closed forms would give NaN, or weights that grow with the distance).
-  if (fabs(t[0]) < 1.0 && fabs(t[1]) < 1.0 && fabs(t[2]) < 1.0)
+  // closed forms would give NaN, or weights that grow with the distance).  t = 1
+  // is in reach: X - floor(X) rounds to it just below a node (a walled y of -1e-20),
+  // and the closed forms then give the weights of that node.
+  if (in_reach<K>(t[0]) && in_reach<K>(t[1]) && in_reach<K>(t[2]))
     s.W = node_weight<K, double>(kx, t[0], q[0]) * node_weight<K, double>(ky, t[1], q[1]) *
           node_weight<K, double>(kz, t[2], q[2]);
   s.site = true;
