@@ -170,14 +170,16 @@ class Lattice:
 
     def __init__(self, nx, ny, nz, wall_y=0, max_particles=0, max_bonds=0, max_shells=0,
                  max_shell_size=0, stream=None, device="cuda", _ctx=None, static_workspace=False,
-                 **params):
+                 _work_stream=None, **params):
         import torch
         self.torch = torch
+        self._keep = self._keep_p = ()  # uploads that the enqueued work reads
         if _ctx is not None:  # a slot of an ensemble: the ensemble owns memory and stream
             self.grid = lb_grid(int(nx), int(ny), int(nz), int(wall_y))
             self.params = make_params(**params)
             self.device = torch.device(device)
             self.stream = stream
+            self._work_stream = _work_stream
             self.workspace = None
             self.ctx = _ctx
             self.shape = (int(nz), int(ny), int(nx))
@@ -192,6 +194,7 @@ class Lattice:
                                 int(max_shell_size))
         self.device = torch.device(device)
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
+        self._work_stream = self.stream
         self.shape = (int(nz), int(ny), int(nx))
         self.N = int(nx) * int(ny) * int(nz)
         self.np = 0
@@ -220,16 +223,21 @@ class Lattice:
         t = self.torch.as_tensor(t, dtype=self.torch.float64, device=self.device)
         return t.reshape(shape).contiguous()
 
-    def _inputs_ready(self, *given):
+    def _inputs_ready(self, kept, *given):
         """Waits until the arrays given by the caller can be read from any
         stream: for the whole device where one is a device tensor (the stream it
         was made on is not known), else for the current stream, on which _f64
         copied them (a wait for the device would also wait for work of others,
-        such as the copies of a server's results)."""
+        such as the copies of a server's results).  kept: the arrays of the last
+        such call, which this one replaces; their memory goes back to the current
+        stream's pool, so the lattice's own stream, on which they are read, is
+        waited for as well."""
         if any(isinstance(t, self.torch.Tensor) and t.is_cuda for t in given):
             self.torch.cuda.synchronize(self.device)
-        else:
-            self.torch.cuda.current_stream(self.device).synchronize()
+            return
+        self.torch.cuda.current_stream(self.device).synchronize()
+        if any(t is not None for t in kept):
+            self._work_stream.synchronize()
 
     def _call(self, name, *args):
         _check(getattr(load(), name)(self.ctx, *args), self.ctx)
@@ -238,7 +246,7 @@ class Lattice:
     def lb_init_fluid(self, rho=None, u=None):
         r = None if rho is None else self._f64(rho, self.shape)
         v = None if u is None else self._f64(u, (3,) + self.shape)
-        self._inputs_ready(rho, u)
+        self._inputs_ready(self._keep, rho, u)
         self._call("lb_init_fluid", _ptr(r), _ptr(v))
         self._keep = (r, v)
 
@@ -247,7 +255,7 @@ class Lattice:
         n = p.shape[0]
         v = None if vel is None else self._f64(vel, (n, 3))
         m = None if mass is None else self._f64(mass, (n,))
-        self._inputs_ready(pos, vel, mass)
+        self._inputs_ready(self._keep_p, pos, vel, mass)
         self._call("lb_set_particles", n, _ptr(p), _ptr(v), _ptr(m))
         self._keep_p = (p, v, m)
         self.np = n
@@ -391,7 +399,9 @@ class Ensemble:
         if st == LB_EBUSY:
             return None
         _echeck(st, self.ens)
-        lat = Lattice(nx, ny, nz, stream=None, device=self.device, _ctx=ctx, **params)
+        lat = Lattice(nx, ny, nz, stream=None, device=self.device, _ctx=ctx,
+                      _work_stream=self.torch.cuda.ExternalStream(self.stream_ptr, self.device),
+                      **params)
         self.slots[slot.value] = lat
         return slot.value, lat
 

@@ -1,0 +1,71 @@
+"""Lattices on a stream of their own: the host arrays of one call stay intact
+until the lattice's stream has read them, however far the host runs ahead (here
+everything is enqueued behind a wait of that stream).  Every run equals the same
+sequence with a wait after each call, within the rounding of unordered FP32 sums
+(a mixed-up upload differs by whole sites)."""
+import numpy as np
+import pytest
+
+from paper_1406_2211_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+BOX, N, RUNS, STEPS = (48, 40, 36), 600, 6, 5
+
+
+def _lattice(side):
+    import torch
+    from paper_1406_2211_amd import lbc as L
+    stream = torch.cuda.Stream() if side else None
+    lat = L.Lattice(*BOX, max_particles=N, stream=stream, tau=0.8, coupling=L.LB_COUPLE_FC, gamma=1.0,
+                    storage=L.LB_F32)
+    lat.lb_step(1)  # the kernels are loaded
+    torch.cuda.synchronize()
+    if side:
+        with torch.cuda.stream(stream):
+            torch.cuda._sleep(200_000_000)  # cycles: 0.1 s or more
+    return lat
+
+
+def _particle_runs(side):
+    import torch
+    g = np.random.default_rng(5)
+    given = [(I.uniform_positions(N, BOX, 50 + k), g.normal(0.0, 1e-3, (N, 3)), np.ones(N)) for k in range(RUNS)]
+    lat, out = _lattice(side), []
+    for p in given:
+        lat.lb_set_particles(*p)
+        lat.lb_step(STEPS)
+        if len(out) < 2:  # (a later one would take the memory of an upload)
+            out.append(lat.lb_get_particles())
+        if not side:
+            torch.cuda.synchronize()
+    torch.cuda.synchronize()
+    return [p.cpu().numpy() for p, _ in out]
+
+
+def test_particle_uploads_on_a_side_stream():
+    print("[gpu] particle uploads on a side stream", flush=True)
+    for x, y in zip(_particle_runs(True), _particle_runs(False)):
+        d = x - y
+        d -= np.array(BOX) * np.round(d / np.array(BOX))
+        assert np.abs(d).max() < 1e-4
+
+
+def _fluid_runs(side):
+    import torch
+    given = [I.noise_velocity((BOX[2], BOX[1], BOX[0]), 1e-3 * (k + 1), k) for k in range(RUNS)]
+    lat, out = _lattice(side), []
+    for u in given:
+        lat.lb_init_fluid(None, u)
+        lat.lb_step(STEPS)
+        if len(out) < 2:
+            out.append(lat.lb_moments())
+        if not side:
+            torch.cuda.synchronize()
+    torch.cuda.synchronize()
+    return [u.cpu().numpy() for _, u in out]
+
+
+def test_fluid_uploads_on_a_side_stream():
+    print("[gpu] fluid uploads on a side stream", flush=True)
+    for x, y in zip(_fluid_runs(True), _fluid_runs(False)):
+        assert np.abs(x - y).max() <= 1e-5 * np.abs(y).max()
