@@ -225,14 +225,15 @@ class Lattice:
 
     def _inputs_ready(self, kept, *given):
         """Waits until the arrays given by the caller can be read from any
-        stream: for the whole device where one is a device tensor (the stream it
-        was made on is not known), else for the current stream, on which _f64
-        copied them (a wait for the device would also wait for work of others,
-        such as the copies of a server's results).  kept: the arrays of the last
-        such call, which this one replaces; their memory goes back to the current
-        stream's pool, so the lattice's own stream, on which they are read, is
-        waited for as well."""
-        if any(isinstance(t, self.torch.Tensor) and t.is_cuda for t in given):
+        stream: for the whole device where one may be device memory (any object but
+        a host array or host tensor; the stream it was made on is not known), else
+        for the current stream, on which _f64 copied them (a wait for the device
+        would also wait for work of others, such as the copies of a server's
+        results).  kept: the arrays of the last such call, which this one replaces;
+        their memory goes back to the current stream's pool, so the lattice's own
+        stream, on which they are read, is waited for as well."""
+        if not all(t is None or isinstance(t, np.ndarray) or
+                   (isinstance(t, self.torch.Tensor) and t.device.type == "cpu") for t in given):
             self.torch.cuda.synchronize(self.device)
             return
         self.torch.cuda.current_stream(self.device).synchronize()

@@ -69,3 +69,38 @@ def test_fluid_uploads_on_a_side_stream():
     print("[gpu] fluid uploads on a side stream", flush=True)
     for x, y in zip(_fluid_runs(True), _fluid_runs(False)):
         assert np.abs(x - y).max() <= 1e-5 * np.abs(y).max()
+
+
+class _Foreign:
+    """Device memory of another library: an object with __cuda_array_interface__."""
+
+    def __init__(self, t):
+        self.t = t
+
+    @property
+    def __cuda_array_interface__(self):
+        return self.t.__cuda_array_interface__
+
+
+@pytest.mark.parametrize("which", ["particles", "fluid"])
+def test_foreign_device_arrays_are_waited_for(which):
+    """Device arrays that are no torch tensors, written on a stream that the call
+    does not know: read when that stream is done."""
+    import torch
+    print(f"[gpu] foreign arrays, {which}", flush=True)
+    shape = (N, 3) if which == "particles" else (3, BOX[2], BOX[1], BOX[0])
+    g = np.random.default_rng(8)
+    values = torch.from_numpy(g.uniform(1.0, 30.0, shape) * (1.0 if which == "particles" else 1e-4)).cuda()
+    given, other = torch.ones_like(values), torch.cuda.Stream()
+    lat = _lattice(False)
+    with torch.cuda.stream(other):
+        torch.cuda._sleep(200_000_000)
+        given.copy_(values)
+    if which == "particles":
+        lat.lb_set_particles(_Foreign(given), np.zeros((N, 3)), np.ones(N))
+        got = lat.lb_get_particles()[0]
+    else:
+        lat.lb_init_fluid(None, _Foreign(given))
+        got = lat.lb_moments()[1]
+    torch.cuda.synchronize()
+    assert float((got - values).abs().max()) <= 1e-5 * float(values.abs().max())
