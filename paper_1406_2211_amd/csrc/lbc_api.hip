@@ -989,10 +989,10 @@ static lb_status create_ctx(const lb_grid* g, const lb_params* p, const lb_limit
   c->geo.ny = g->ny;
   c->geo.nz = g->nz;
   c->geo.wall = g->wall_y;
-  // Row-aligned mask words (and the row-per-workgroup lattice pass) when x is
-  // a multiple of 64; otherwise one word per 64 consecutive linear sites and
+  // Row-aligned mask words (and the row-per-workgroup lattice pass) where the
+  // rows allow it; otherwise one word per 64 consecutive linear sites and
   // the linear-site pass.
-  c->geo.wpr = (linear_mask || g->nx % 64 != 0) ? 0 : g->nx / 64;
+  c->geo.wpr = (linear_mask || !rows_fit(g->nx, storage_bytes(p->storage))) ? 0 : g->nx / 64;
   c->member = linear_mask;
   c->geo.N = (long long)g->nx * g->ny * g->nz;
   c->geo.ps = pop_stride(c->geo.N);

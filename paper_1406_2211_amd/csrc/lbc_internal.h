@@ -25,6 +25,12 @@ inline bool big_box(const Geo& g, int storage) {
   return (unsigned long long)g.N * (storage == LB_F64 ? 8 : (storage == LB_F32 ? 4 : 2)) > 0xffffffffull;
 }
 
+// Whether a box takes the row-mapped launches: rows of whole 64-site mask words,
+// whose byte offsets the lanes hold in 32 bits.  Others take the linear-site pass.
+inline bool rows_fit(int nx, int storage_bytes) {
+  return nx % 64 == 0 && (unsigned long long)nx * storage_bytes <= 0xffffffffull;
+}
+
 // floor(2^32 / d), the multiplier of div_rem (2^32 - 1 for d = 1).
 inline uint32_t div_magic(int d) {
   return d <= 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (unsigned)d);

@@ -11,6 +11,7 @@ SOURCE = r"""
 #include "lbc_internal.h"
 using namespace lbc;
 extern "C" int order_pays_c(int sb, int K, long long np, long long N) { return order_pays(sb, K, np, N); }
+extern "C" int rows_fit_c(int nx, int sb) { return rows_fit(nx, sb); }
 """
 
 
@@ -37,3 +38,13 @@ def test_tile_order_is_not_taken_by_16_bit_boxes(rules, K):
     for sb in (4, 8):
         N = 4096 * K * K * 128 // sb  # one row of nodes per line
         assert f(sb, K, 4096, N) and not f(sb, K, 4095, N) and not f(sb, K, 4096, N + 128)
+
+
+def test_rows_beyond_32_bit_offsets_take_the_linear_site_pass(rules):
+    """The row-mapped pass holds x times the stored size in 32 bits; longer rows,
+    which the grid check admits, go to the pass that has a 64-bit form."""
+    for sb in (2, 4, 8):
+        most = (2**32 - 1) // sb // 64 * 64  # the longest row whose offsets fit
+        for nx in (64, 128, most, min(most + 64, 2**31 - 64)):
+            assert bool(rules.rows_fit_c(nx, sb)) == (nx * sb < 2**32), (nx, sb)
+        assert not rules.rows_fit_c(100, sb) and not rules.rows_fit_c(most - 1, sb)
