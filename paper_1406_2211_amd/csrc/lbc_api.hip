@@ -201,6 +201,7 @@ struct lb_ctx {
   std::vector<int32_t> bonds;
   double bond_k = 0, bond_r0 = 1;
   int bond_type = LB_HARMONIC;
+  double image_lo[3], image_hi[3];  // image_bounds of the box
   bool groups_dirty = true;
   int ngroups = 0, gcap = 64;
   bool tiled = false;   // binned LDS-staged particle path (dense IB markers)
@@ -333,9 +334,10 @@ static BondArgs bond_args(const lb_ctx* c, double* pos) {
   b.fint = c->L.fint;
   b.k = c->bond_k;
   b.r0 = c->bond_r0;
-  b.rL[0] = 1.0 / c->geo.nx;
-  b.rL[1] = 1.0 / c->geo.ny;
-  b.rL[2] = 1.0 / c->geo.nz;
+  for (int k = 0; k < 3; ++k) {
+    b.lo[k] = c->image_lo[k];
+    b.hi[k] = c->image_hi[k];
+  }
   b.type = c->bond_type;
   return b;
 }
@@ -995,6 +997,9 @@ static lb_status create_ctx(const lb_grid* g, const lb_params* p, const lb_limit
   c->geo.wpr = (linear_mask || !rows_fit(g->nx, storage_bytes(p->storage))) ? 0 : g->nx / 64;
   c->member = linear_mask;
   c->geo.N = (long long)g->nx * g->ny * g->nz;
+  image_bounds(g->nx, c->image_lo[0], c->image_hi[0]);
+  image_bounds(g->ny, c->image_lo[1], c->image_hi[1]);
+  image_bounds(g->nz, c->image_lo[2], c->image_hi[2]);
   c->geo.ps = pop_stride(c->geo.N);
   c->L = carve(*g, *p, *lim, d_workspace);
   c->tiled = p->coupling == LB_COUPLE_IB && p->kernel >= 3;

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <cmath>
 #include <stdint.h>
 
 #include "lbc.h"
@@ -36,6 +37,20 @@ inline uint32_t div_magic(int d) {
   return d <= 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (unsigned)d);
 }
 
+// Bounds of the nearest image in a box of length L: floor(d/L + 1/2), rounded as
+// written, is -1 for d < lo, 0 for lo <= d < hi and 1 from hi on (|d| <= L); two
+// compares for a division.  (A product with 1/L rounds otherwise: for a third of all
+// L it takes another image one unit in the last place below half a box.)
+inline void image_bounds(double L, double& lo, double& hi) {
+  const auto image = [L](double d) { return std::floor(d / L + 0.5); };
+  hi = 0.5 * L;
+  while (image(hi) >= 1.0) hi = std::nextafter(hi, 0.0);
+  while (image(hi) < 1.0) hi = std::nextafter(hi, L);
+  lo = -0.5 * L;
+  while (image(lo) >= 0.0) lo = std::nextafter(lo, -L);
+  while (image(lo) < 0.0) lo = std::nextafter(lo, 0.0);
+}
+
 struct BondArgs {
   Geo g;
   const int32_t* perm;   // particles ordered by group
@@ -48,7 +63,7 @@ struct BondArgs {
   const double* mass;
   double* fint;
   double k, r0;
-  double rL[3];  // 1/nx, 1/ny, 1/nz
+  double lo[3], hi[3];  // image_bounds of nx, ny, nz
   int type;
 };
 

@@ -3,6 +3,7 @@ import ctypes as C
 import os
 import subprocess
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -12,6 +13,7 @@ SOURCE = r"""
 using namespace lbc;
 extern "C" int order_pays_c(int sb, int K, long long np, long long N) { return order_pays(sb, K, np, N); }
 extern "C" int rows_fit_c(int nx, int sb) { return rows_fit(nx, sb); }
+extern "C" void image_bounds_c(double L, double* b) { image_bounds(L, b[0], b[1]); }
 """
 
 
@@ -48,3 +50,25 @@ def test_rows_beyond_32_bit_offsets_take_the_linear_site_pass(rules):
         for nx in (64, 128, most, min(most + 64, 2**31 - 64)):
             assert bool(rules.rows_fit_c(nx, sb)) == (nx * sb < 2**32), (nx, sb)
         assert not rules.rows_fit_c(100, sb) and not rules.rows_fit_c(most - 1, sb)
+
+
+def test_nearest_image_is_that_of_the_division(rules):
+    """Two compares with the bounds give floor(d/L + 1/2) as the division rounds
+    it, at every d within four units in the last place of half a box and over
+    the whole range of |d| <= L."""
+    f = rules.image_bounds_c
+    f.argtypes = [C.c_double, C.c_void_p]
+    lengths = list(range(1, 3000)) + [4095, 4097, 65535, 99991, 2**20 + 1, 2**24 - 1, 2**30 + 7, 2**31 - 1]
+    for n in lengths:
+        L, b = float(n), np.zeros(2)
+        f(L, b.ctypes.data)
+        d = [0.0, L, -L, np.nextafter(L, 0), np.nextafter(-L, 0)]
+        for h in (0.5 * L, -0.5 * L):
+            up = down = h
+            d.append(h)
+            for _ in range(4):
+                up, down = np.nextafter(up, np.inf), np.nextafter(down, -np.inf)
+                d += [up, down]
+        d = np.concatenate([d, np.linspace(-L, L, 41)])
+        image = np.where(d >= b[1], 1.0, np.where(d < b[0], -1.0, 0.0))
+        assert (image == np.floor(d / L + 0.5)).all(), n
