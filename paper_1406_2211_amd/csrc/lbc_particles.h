@@ -33,12 +33,13 @@ struct SiteSlot {
   int j0[3];    // first stencil node, unwrapped
 };
 
-// Whether t of stencil_t is that of a position near its first node: [0, 1], or
-// [-1/2, 1/2] and the rounding of X + 1/2 for the 3-point kernel (whose square root
-// exists up to 0.577).
+// Whether t of stencil_t is that of a position near its first node: at most 1, or
+// 1/2 and the rounding of X + 1/2 for the 3-point kernel (whose square root exists
+// up to 0.577).  One compare per axis, in every lane's chain: with two (t >= 0 as
+// well, which only clamped positions miss) one particle at 32^3 took 1 % longer.
 template <int K>
 __device__ __forceinline__ bool in_reach(double t) {
-  return K == 3 ? fabs(t) <= 0.5625 : (t >= 0.0 && t <= 1.0);
+  return fabs(t) <= (K == 3 ? 0.5625 : 1.0);
 }
 
 template <int K>
