@@ -407,18 +407,18 @@ __device__ __forceinline__ void load_partners(const BondArgs& b, long long p, Pa
   for (int k = 0; k < kMaxBondsReg; ++k) P.loc[k] = (k < P.n) ? b.loc[b.nbr[e0 + k]] : 0;
 }
 
-// d - L floor(d/L + 1/2) for |d| < 3L/2 (positions are wrapped into [0, L]).
-__device__ __forceinline__ double nearest_image(double d, double L, double lo, double hi) {
-  return d - (d >= hi ? L : (d < lo ? -L : 0.0));
+// d - n floor(d/n + 1/2) for |d| < 3n/2 (positions are wrapped into [0, n]).
+__device__ __forceinline__ double nearest_image(double d, int n, double lo, double hi) {
+  return d - (double)(d >= hi ? n : (d < lo ? -n : 0));
 }
 
 __device__ __forceinline__ void bond_pair(const BondArgs& b, const double r[3], const double* q,
                                           double F[3]) {
   double d[3];
   for (int k = 0; k < 3; ++k) d[k] = q[k] - r[k];
-  d[0] = nearest_image(d[0], (double)b.g.nx, b.lo[0], b.hi[0]);
-  if (!b.g.wall) d[1] = nearest_image(d[1], (double)b.g.ny, b.lo[1], b.hi[1]);
-  d[2] = nearest_image(d[2], (double)b.g.nz, b.lo[2], b.hi[2]);
+  d[0] = nearest_image(d[0], b.g.nx, b.lo[0], b.hi[0]);
+  if (!b.g.wall) d[1] = nearest_image(d[1], b.g.ny, b.lo[1], b.hi[1]);
+  d[2] = nearest_image(d[2], b.g.nz, b.lo[2], b.hi[2]);
   const double L = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
   double s;
   if (b.type == LB_FENE)  // infinite energy from L = r0 on: NaN, not the formula's sign flip
