@@ -129,7 +129,7 @@ def serve_batched(requests, pool_bytes, max_slots=64, storage=L.LB_F16, chunk=20
     # Kept fields are copied to the host by a thread beside the steps of the
     # boxes still running (24 requests, six kept: 43 of 86 ms went into copies
     # that the device waited for).  A kept request is complete when its copy is.
-    copier = _FieldCopier(ens.device) if keep else None
+    copier = _FieldCopier(ens.device) if keep is not None else None
     copies = []
     t0 = time.perf_counter()
     tuned = not autotune
