@@ -109,7 +109,8 @@ class _FieldCopier:
         return time.perf_counter()
 
     def close(self):
-        self.pool.shutdown()
+        """Waits for the copies that have begun, drops the others and ends the threads."""
+        self.pool.shutdown(cancel_futures=True)
 
 
 def serve_batched(requests, pool_bytes, max_slots=64, storage=L.LB_F16, chunk=20, comoving=1,
@@ -133,58 +134,60 @@ def serve_batched(requests, pool_bytes, max_slots=64, storage=L.LB_F16, chunk=20
     copies = []
     t0 = time.perf_counter()
     tuned = not autotune
-    while pending or queue or active:
-        now = time.perf_counter() - t0
-        while pending and pending[0].arrival <= now:
-            queue.append(pending.pop(0))
-        ta = clock()
-        while queue:  # continuous admission: FIFO order, as far as memory and slots allow
-            req = queue[0]
-            got = ens.admit(req.side, req.side, req.side, req.steps, max_particles=req.nparticles,
-                            **request_params(req, storage, comoving=comoving))
-            if got is None:
-                break
-            queue.pop(0)
-            slot, lat = got
-            _init_box(lat, req)
-            active[slot] = (req, lat, time.perf_counter() - t0)
-        acc["admit_s"] += clock() - ta
-        if not active:
-            if pending:
-                time.sleep(max(0.0, min(0.002, pending[0].arrival - now)))
-            continue
-        if not tuned and len(active) >= 4:
-            ens.autotune(1)
-            tuned = True
-        te = clock()
-        ens.step(chunk)
-        acc["chunks"] += 1
-        tp = clock()
-        acc["enqueue_s"] += tp - te
-        for slot in list(active):
-            done_steps, done = ens.query(slot)
-            if not done:
+    try:
+        while pending or queue or active:
+            now = time.perf_counter() - t0
+            while pending and pending[0].arrival <= now:
+                queue.append(pending.pop(0))
+            ta = clock()
+            while queue:  # continuous admission: FIFO order, as far as memory and slots allow
+                req = queue[0]
+                got = ens.admit(req.side, req.side, req.side, req.steps, max_particles=req.nparticles,
+                                **request_params(req, storage, comoving=comoving))
+                if got is None:
+                    break
+                queue.pop(0)
+                slot, lat = got
+                _init_box(lat, req)
+                active[slot] = (req, lat, time.perf_counter() - t0)
+            acc["admit_s"] += clock() - ta
+            if not active:
+                if pending:
+                    time.sleep(max(0.0, min(0.002, pending[0].arrival - now)))
                 continue
-            req, lat, t_adm = active.pop(slot)
-            tot = lat.lb_totals()
-            if keep is not None and req.rid in keep:
-                _, u = lat.lb_moments()
-                ready = torch.cuda.ExternalStream(ens.stream_ptr, ens.device).record_event()
-                copies.append((len(results), copier.submit(u, ready)))
-                del u
-            t_done = time.perf_counter() - t0
-            results.append(Result(req.rid, req.arrival, t_adm, t_done, req.steps,
-                                  req.side ** 3, tot))
-            ens.retire(slot)
-            if log:
-                log(f"done {req.rid} L={req.side} steps={req.steps} latency={t_done - req.arrival:.3f}s")
-        acc["poll_s"] += clock() - tp
-    for k, (host, parts) in copies:
-        results[k].completed = max(c.result() for c in parts) - t0
-        fields[results[k].rid] = host
-    if copier:
-        copier.close()
-    ens.destroy()
+            if not tuned and len(active) >= 4:
+                ens.autotune(1)
+                tuned = True
+            te = clock()
+            ens.step(chunk)
+            acc["chunks"] += 1
+            tp = clock()
+            acc["enqueue_s"] += tp - te
+            for slot in list(active):
+                done_steps, done = ens.query(slot)
+                if not done:
+                    continue
+                req, lat, t_adm = active.pop(slot)
+                tot = lat.lb_totals()
+                if keep is not None and req.rid in keep:
+                    _, u = lat.lb_moments()
+                    ready = torch.cuda.ExternalStream(ens.stream_ptr, ens.device).record_event()
+                    copies.append((len(results), copier.submit(u, ready)))
+                    del u
+                t_done = time.perf_counter() - t0
+                results.append(Result(req.rid, req.arrival, t_adm, t_done, req.steps,
+                                      req.side ** 3, tot))
+                ens.retire(slot)
+                if log:
+                    log(f"done {req.rid} L={req.side} steps={req.steps} latency={t_done - req.arrival:.3f}s")
+            acc["poll_s"] += clock() - tp
+        for k, (host, parts) in copies:
+            results[k].completed = max(c.result() for c in parts) - t0
+            fields[results[k].rid] = host
+    finally:  # also where a request or the caller's log raised
+        if copier:
+            copier.close()
+        ens.destroy()
     if prof is not None:
         prof.update({k: round(v, 4) if isinstance(v, float) else v for k, v in acc.items()})
     torch.cuda.synchronize()
