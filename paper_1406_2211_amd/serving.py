@@ -17,6 +17,7 @@ from __future__ import annotations
 
 import math
 import time
+from collections import deque
 from concurrent.futures import ThreadPoolExecutor
 from dataclasses import dataclass, field
 
@@ -80,7 +81,10 @@ class _FieldCopier:
     """Copies device fields to host arrays in threads, beside the work that
     follows them on their stream.  A thread copies one component at a time on a
     stream of its own: the copies go through pageable memory, and a single
-    thread moves about 6 GB/s."""
+    thread moves about 6 GB/s.  The fields under way take device memory beside
+    the pool: `most` bytes of them, or one field."""
+
+    most = 1 << 30
 
     def __init__(self, device, threads=4):
         import torch
@@ -88,6 +92,13 @@ class _FieldCopier:
         self.pool = ThreadPoolExecutor(max_workers=threads)
         self.streams = [torch.cuda.Stream(device) for _ in range(threads)]
         self.turn = 0
+        self.flying = deque()  # (bytes, copies) of each field handed in, oldest first
+
+    def make_room(self, nbytes):
+        """Waits for the oldest fields until one of nbytes fits beside the others."""
+        while self.flying and sum(b for b, _ in self.flying) + nbytes > self.most:
+            for c in self.flying.popleft()[1]:
+                c.result()
 
     def submit(self, field, ready):
         """Host array of the field and the copies that fill it once the event
@@ -100,6 +111,7 @@ class _FieldCopier:
             self.turn += 1
             stream.wait_event(ready)
             copies.append(self.pool.submit(self._copy, field[a], host[a], stream))
+        self.flying.append((host.nbytes, copies))
         return host, copies
 
     def _copy(self, src, dst, stream):
@@ -170,7 +182,12 @@ def serve_batched(requests, pool_bytes, max_slots=64, storage=L.LB_F16, chunk=20
                 req, lat, t_adm = active.pop(slot)
                 tot = lat.lb_totals()
                 if keep is not None and req.rid in keep:
-                    _, u = lat.lb_moments()
+                    copier.make_room(24 * lat.N)
+                    try:
+                        _, u = lat.lb_moments()
+                    except torch.OutOfMemoryError:  # the fields under way may hold what is short
+                        copier.make_room(math.inf)
+                        _, u = lat.lb_moments()
                     ready = torch.cuda.ExternalStream(ens.stream_ptr, ens.device).record_event()
                     copies.append((len(results), copier.submit(u, ready)))
                     del u
