@@ -213,6 +213,7 @@ struct lb_ctx {
   bool running = false;  // ensemble slot whose device record has been uploaded
   bool first_done = false;  // the coming step's first coupling half is done (couple_second)
   bool mvalid = false;   // coupling moment cache holds the state of f[cur]
+  int dev = -1;          // the GPU that was current when the context was made
   int lds_cu = 0;        // LDS bytes per compute unit (for the lattice-pass occupancy cap)
   int nshell = 0, shell_size = 0;
   double k_tether = 0;
@@ -1013,7 +1014,8 @@ static lb_status create_ctx(const lb_grid* g, const lb_params* p, const lb_limit
   }
   {
     int dev = 0, v = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
+    if (hipGetDevice(&dev) == hipSuccess) c->dev = dev;
+    if (c->dev >= 0 &&
         hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) ==
             hipSuccess)
       c->lds_cu = v;
@@ -1180,9 +1182,29 @@ lb_status lb_stress_sweep(lb_ctx* c, void* d_sigma) {
   return LB_OK;
 }
 
+// Whether a kernel of the context may write to p: memory of its own GPU (or null).
+// Another GPU's is out of a kernel's reach unless the two are peers, and the
+// runtime's copies serve every kind of memory.
+static bool own_memory(const lb_ctx* c, const void* p) {
+  if (!p) return true;
+  hipPointerAttribute_t at;
+  if (hipPointerGetAttributes(&at, p) == hipSuccess)
+    return at.type == hipMemoryTypeDevice && at.device == c->dev;
+  (void)hipGetLastError();
+  return false;
+}
+
 lb_status lb_get_particles(lb_ctx* c, double* d_pos, double* d_vel) {
   if (!c) return fail(nullptr, LB_EINVAL, "null context");
-  HIPCHK(c, launch_copy_particles(c->np, c->L.pos, c->L.vel, d_pos, d_vel, c->st));
+  if (c->np <= 0) return LB_OK;
+  if (own_memory(c, d_pos) && own_memory(c, d_vel)) {
+    HIPCHK(c, launch_copy_particles(c->np, c->L.pos, c->L.vel, d_pos, d_vel, c->st));
+    return LB_OK;
+  }
+  if (d_pos)
+    HIPCHK(c, hipMemcpyAsync(d_pos, c->L.pos, c->np * 24, hipMemcpyDeviceToDevice, c->st));
+  if (d_vel)
+    HIPCHK(c, hipMemcpyAsync(d_vel, c->L.vel, c->np * 24, hipMemcpyDeviceToDevice, c->st));
   return LB_OK;
 }
 
