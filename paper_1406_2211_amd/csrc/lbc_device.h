@@ -247,19 +247,6 @@ __device__ __forceinline__ void flag_site(uint64_t* mw, uint64_t bit) {
   if (!(*mw & bit)) atomicOr((unsigned long long*)mw, bit);
 }
 
-// Quotient and remainder of n / d for 32-bit n and d >= 1, with m =
-// div_magic(d) from the host: n m / 2^32 lies in (n/d - 1, n/d], so its floor is
-// the quotient or one less, and one correction step fixes it.
-__device__ __forceinline__ uint32_t div_rem(uint32_t n, uint32_t d, uint32_t m, uint32_t& rem) {
-  uint32_t q = (uint32_t)(((uint64_t)n * m) >> 32), r = n - q * d;
-  if (r >= d) {
-    q += 1;
-    r -= d;
-  }
-  rem = r;
-  return q;
-}
-
 // A stored population in the compute type R of the caller.
 template <int S, typename R>
 __device__ __forceinline__ R pull_value(const typename Store<S>::T* p, R inv) {

@@ -37,6 +37,19 @@ inline uint32_t div_magic(int d) {
   return d <= 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (unsigned)d);
 }
 
+// Quotient and remainder of n / d for 32-bit n and d >= 1, with m =
+// div_magic(d) from the host: n m / 2^32 lies in (n/d - 1, n/d], so its floor is
+// the quotient or one less, and one correction step fixes it.
+__host__ __device__ __forceinline__ uint32_t div_rem(uint32_t n, uint32_t d, uint32_t m, uint32_t& rem) {
+  uint32_t q = (uint32_t)(((uint64_t)n * m) >> 32), r = n - q * d;
+  if (r >= d) {
+    q += 1;
+    r -= d;
+  }
+  rem = r;
+  return q;
+}
+
 // Bounds of the nearest image in a box of length L: floor(d/L + 1/2), rounded as
 // written, is -1 for d < lo, 0 for lo <= d < hi and 1 from hi on (|d| <= L); two
 // compares for a division.  (A product with 1/L rounds otherwise: for a third of all

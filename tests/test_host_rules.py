@@ -14,6 +14,9 @@ using namespace lbc;
 extern "C" int order_pays_c(int sb, int K, long long np, long long N) { return order_pays(sb, K, np, N); }
 extern "C" int rows_fit_c(int nx, int sb) { return rows_fit(nx, sb); }
 extern "C" void image_bounds_c(double L, double* b) { image_bounds(L, b[0], b[1]); }
+extern "C" void div_rem_c(const uint32_t* n, long long count, uint32_t d, uint32_t* q, uint32_t* r) {
+  for (long long i = 0; i < count; ++i) q[i] = div_rem(n[i], d, div_magic((int)d), r[i]);
+}
 """
 
 
@@ -72,3 +75,19 @@ def test_nearest_image_is_that_of_the_division(rules):
         d = np.concatenate([d, np.linspace(-L, L, 41)])
         image = np.where(d >= b[1], 1.0, np.where(d < b[0], -1.0, 0.0))
         assert (image == np.floor(d / L + 0.5)).all(), n
+
+
+@pytest.mark.parametrize("d", [1, 2, 3, 5, 7, 45, 63, 64, 65, 117, 150, 255, 256, 257, 1000, 4095, 4097, 65535, 65536,
+                               65537, 2**30, 2**31 - 1])
+def test_quotient_of_the_linear_site_pass(rules, d):
+    """div_rem with div_magic, as the kernels call them: the exact quotient and
+    remainder of every 32-bit site index by a box side."""
+    g = np.random.default_rng(d)
+    k = g.integers(0, 2**32 // d, 50000, dtype=np.uint64) * np.uint64(d)  # multiples and their neighbours
+    n = np.concatenate([g.integers(0, 2**32, 200000, dtype=np.uint64), np.arange(2000, dtype=np.uint64),
+                        2**32 - 1 - np.arange(2000, dtype=np.uint64), k, k + np.uint64(1), k - np.uint64(1)])
+    n = n[n < 2**32].astype(np.uint32)
+    q, r = np.empty_like(n), np.empty_like(n)
+    rules.div_rem_c(n.ctypes.data_as(C.c_void_p), C.c_longlong(n.size), C.c_uint32(d), q.ctypes.data_as(C.c_void_p),
+                    r.ctypes.data_as(C.c_void_p))
+    assert (q == n // np.uint32(d)).all() and (r == n % np.uint32(d)).all()
