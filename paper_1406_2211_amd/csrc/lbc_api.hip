@@ -181,8 +181,9 @@ bool check_params(const lb_grid* g, const lb_params* p, const lb_limits* lim, st
   return true;
 }
 
-// Steps between two binnings of IB markers into tiles.
-constexpr int64_t kRebin = 32;  // default steps between two marker binnings
+// Steps between two binnings into tiles: of IB markers by default
+// (lb_params::ib_rebin), and of free particles processed in tile order.
+constexpr int64_t kRebin = 32;
 
 }  // namespace
 
@@ -205,7 +206,7 @@ struct lb_ctx {
   bool groups_dirty = true;
   int ngroups = 0, gcap = 64;
   bool tiled = false;   // binned LDS-staged particle path (dense IB markers)
-  int64_t binned_at = -1;  // step of the last marker binning (-1: markers changed since)
+  int64_t binned_at = -1;  // step of the last binning (-1: the particles changed since)
   bool adv_pending = false;  // tiled IB: the final half advection of the last step is due
   uint32_t ustamp = 0;  // tiled IB: stamp of the last velocity pass over the flagged sites
   bool flags_follow = false;  // tiled IB: the force mask holds the markers' last stencils

@@ -51,7 +51,7 @@ __host__ __device__ __forceinline__ uint32_t div_rem(uint32_t n, uint32_t d, uin
 }
 
 // Bounds of the nearest image in a box of length L: floor(d/L + 1/2), rounded as
-// written, is -1 for d < lo, 0 for lo <= d < hi and 1 from hi on (|d| <= L); two
+// written, is -1 for d < lo, 0 for lo <= d < hi and 1 from hi on (|d| < 3L/2); two
 // compares for a division.  (A product with 1/L rounds otherwise: for a third of all
 // L it takes another image one unit in the last place below half a box.)
 inline void image_bounds(double L, double& lo, double& hi) {

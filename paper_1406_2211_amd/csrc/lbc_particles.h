@@ -22,7 +22,7 @@ namespace lbc {
 // dependent loads and instructions, about one wavefront per SIMD, so the chain
 // is kept short: DPP sums, closed-form weights (one square root per axis),
 // one reciprocal per set of divisions (200 particles, 3-point kernel: first
-// half 11 -> 7.4 us, second 11 -> 9.2; 1200 beads, coupled sub-step 8.7 -> 8.4;
+// half 11 -> 7.4 us, second 11 -> 9.2; 1200 beads, coupled sub-step 8.7 -> 8.6;
 // 20 000 particles, first half 15.5 -> 12.8).
 // ======================================================================
 struct SiteSlot {
@@ -407,7 +407,8 @@ __device__ __forceinline__ void load_partners(const BondArgs& b, long long p, Pa
   for (int k = 0; k < kMaxBondsReg; ++k) P.loc[k] = (k < P.n) ? b.loc[b.nbr[e0 + k]] : 0;
 }
 
-// d - n floor(d/n + 1/2) for |d| < 3n/2 (positions are wrapped into [0, n]).
+// d - n floor(d/n + 1/2) for |d| < 3n/2 (positions are wrapped into [0, n]); a
+// coupled sub-step of 1200 beads 8.6 us, with the product by 1/n 8.5.
 __device__ __forceinline__ double nearest_image(double d, int n, double lo, double hi) {
   return d - (double)(d >= hi ? n : (d < lo ? -n : 0));
 }
